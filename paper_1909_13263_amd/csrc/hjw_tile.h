@@ -117,9 +117,6 @@ constexpr int kPartialStride = 5;
 // builtin; everything else is ordinary C++ arithmetic.
 __device__ inline float rcp_t(float x) { return __builtin_amdgcn_rcpf(x); }
 __host__ inline float rcp_t(float x) { return 1.0f / x; }
-__host__ __device__ inline double rcp_t(double x) { return 1.0 / x; }
-__device__ inline double log_t(double x) { return log(x); }
-__host__ inline double log_t(double x) { return std::log(x); }
 __device__ inline float sqrt_t(float x) { return sqrtf(x); }
 __host__ inline float sqrt_t(float x) { return std::sqrt(x); }
 __device__ inline double sqrt_t(double x) { return sqrt(x); }
@@ -180,6 +177,72 @@ __host__ __device__ inline bool finite_t(T x) {
     return __builtin_isfinite(x);  // one class test on the device
 }
 
+// ------------------------------------------------- FP64 quotients, root and logarithm
+// The march's FP64 quotients, square roots and logarithms have arguments in a known range
+// (denominators >= 4 or products of squares, radicands and logarithms' arguments >= 1), so
+// they are written out from the hardware seeds instead of calling the general ones, whose
+// scaling and special cases are most of their instructions and of the FP64 kernels' code.
+// Zeros and denormals do not occur; infinities and NaNs end as NaN, which fails the step.
+// Over 2^20 arguments the seeds' relative errors stay below 5.3e-8 (2^-24).  Cell means of
+// random pairs, wide and narrow, against extended precision: 1.2e-14 at most and 9.2e-16 rms,
+// as with the general division, sqrt and log; q + num / den: 2.2e-16 of it (2.8e-16 before).
+// They took the FP64 16-row stage kernels from 155-167 KB and 168 registers with 2-6 spilled
+// to 106-120 KB and 159-163 with none: level set 512^2 to t = 0.1 12.9 -> 8.7 ms, Burgers
+// 1024^2 16.0 -> 14.6 ms, one-sided derivatives of 1000 x 700 nodes 56 -> 41 us.
+__device__ inline double rcp_seed(double x) { return __builtin_amdgcn_rcp(x); }
+__host__ inline double rcp_seed(double x) { return 1.0 / x; }
+__device__ inline double rsq_seed(double x) { return __builtin_amdgcn_rsq(x); }
+__host__ inline double rsq_seed(double x) { return 1.0 / std::sqrt(x); }
+
+// 1/x to about the square of the seed's error: one Newton step.
+__host__ __device__ inline double rcp_once(double x) {
+    const double r = rcp_seed(x);
+    return fma_t(r, fma_t(-x, r, 1.0), r);
+}
+// 1/x to half an ulp and a bit: r (1 + e + e^2), e = 1 - x r, so that the error left is the
+// cube of the seed's and the rounding of the last sum.
+__host__ __device__ inline double rcp_full(double x) {
+    const double r = rcp_seed(x);
+    const double e = fma_t(-x, r, 1.0);
+    return fma_t(r, fma_t(e, e, e), r);
+}
+// num/den, corrected by its own remainder.
+__host__ __device__ inline double quot(double num, double den) {
+    const double r = rcp_full(den);
+    const double q = mul_rn(num, r);
+    return fma_t(fma_t(-den, q, num), r, q);
+}
+// sqrt(x), x >= 1: the coupled iteration g -> sqrt(x), h -> 1/(2 sqrt(x)) (Goldschmidt), then
+// one correction by the remainder x - g^2.
+__host__ __device__ inline double root(double x) {
+    const double y = rsq_seed(x);
+    double g = mul_rn(x, y), h = 0.5 * y;
+    const double e = fma_t(-h, g, 0.5);
+    g = fma_t(g, e, g);
+    h = fma_t(h, e, h);
+    return fma_t(fma_t(-g, g, x), h, g);
+}
+// ln(y), y >= 1: y = 2^k m, m in [sqrt(1/2), sqrt(2)); ln m = 2 atanh f, f = (m-1)/(m+1), as
+// 2f + f z Q(z), z = f^2 <= 0.0295, Q the degree-6 Chebyshev fit of its series
+// 2/3 + 2z/5 + 2z^2/7 + ... on that range (relative error of ln m below 5e-18).
+__host__ __device__ inline double log_ge1(double y) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, y);
+    const int hi = int(b >> 32);
+    const int k = (hi - 0x3fe6a09e) >> 20;
+    const uint64_t mb = (uint64_t(uint32_t(hi - (k << 20))) << 32) | uint32_t(b);
+    const double m = __builtin_bit_cast(double, mb);
+    const double f = quot(m - 1.0, m + 1.0);
+    const double z = mul_rn(f, f);
+    double q = fma_t(z, 0.14616585424888621989, 0.15331710618210771568);
+    q = fma_t(z, q, 0.18182889455674946039);
+    q = fma_t(z, q, 0.22222211130259877029);
+    q = fma_t(z, q, 0.28571428626003268742);
+    q = fma_t(z, q, 0.39999999999899443233);
+    q = fma_t(z, q, 0.66666666666666696883);
+    const double u = fma_t(f, mul_rn(z, q), f + f);
+    return fma_t(double(k), 0.693147180559945309417, u);
+}
+
 // Relative half-gap below which M comes from the midpoint series, and the
 // series length: the truncation error stays below one unit in the last place
 // (4 terms to 2e-2 in FP64, 3 terms to 1e-1 in FP32).
@@ -194,7 +257,9 @@ template <> struct SeriesCfg<float> { static constexpr float tau2 = 1.0e-2f; };
 // (the Taylor series of the mean about m = sg/2 with y = (h/(1+m^2))^2 = 4 g^2), so
 // (2M)^2 = q4 X^2 needs no square root.  xx receives the squared relative gap dl^2 / q4.
 __host__ __device__ inline double mean2sq_series(double sg, double dl, double q4, double& xx) {
-    const double g = dl / q4;
+    // g enters X only through g^2 <= tau2 / q4 <= 1e-4 wherever the series is used, so the
+    // reciprocal's error, below 2^-46, stays far below the rounding of X
+    const double g = dl * rcp_once(q4);
     xx = dl * g;
     const double g2 = g * g;
     const double s2 = mul_rn(sg, sg);
@@ -218,8 +283,8 @@ __host__ __device__ inline float mean2sq_series(float sg, float dl, float q4, fl
 // gap use it, so that the difference of two values is divided by a gap of at least
 // tau sqrt(4 + sg^2): the rounding is amplified by a small factor only.
 __host__ __device__ inline double prim(double s) {
-    const double r = sqrt_t(fma_t(s, s, 1.0));
-    return 0.5 * fma_t(s, r, copysign(log_t(fabs(s) + r), s));
+    const double r = root(fma_t(s, s, 1.0));
+    return 0.5 * fma_t(s, r, copysign(log_ge1(fabs(s) + r), s));
 }
 // FP32: the same from the hardware square root and base-2 logarithm (about 1 ulp each).
 __device__ inline float prim(float s) {
@@ -233,18 +298,13 @@ __host__ inline float prim(float s) {
     return 0.5f * fma_t(s, r, std::copysign(l, s));
 }
 
-// Quotients: exact division in FP64; in FP32 a product with the hardware reciprocal.
-template <typename T>
-__host__ __device__ inline T wdiv(T num, T den) {
-    return num / den;
-}
-template <>
-__host__ __device__ inline float wdiv<float>(float num, float den) {
-    return num * rcp_t(den);
-}
-// q + num / den: in FP32 one fused multiply-add with the reciprocal.
+// Quotients: corrected by the remainder in FP64; in FP32 a product with the hardware
+// reciprocal.
+__host__ __device__ inline double wdiv(double num, double den) { return quot(num, den); }
+__host__ __device__ inline float wdiv(float num, float den) { return num * rcp_t(den); }
+// q + num / den: one fused multiply-add with the reciprocal (no rounding of the quotient).
 __host__ __device__ inline double add_quot(double q, double num, double den) {
-    return q + num / den;
+    return fma_t(num, rcp_full(den), q);
 }
 __host__ __device__ inline float add_quot(float q, float num, float den) {
     return fma_t(num, rcp_t(den), q);
