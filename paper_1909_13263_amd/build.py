@@ -17,7 +17,9 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-I", INCLUDE, "-I", CSRC]
 # Translation units of the library: the single-grid API and the batched server.
-LIB_SOURCES = ("hjw.hip", "hjw_server.hip")
+LIB_SOURCES = ("hjw.hip", "hjw_resident.hip", "hjw_server.hip")
+# The resident kernels' loop over stages: see hjw_resident.hip.
+EXTRA = {"hjw_resident.hip": ["-mllvm", "-disable-machine-licm"]}
 
 
 def _hipcc():
@@ -36,7 +38,8 @@ def build_library(out: str = LIB) -> str:
     for src in LIB_SOURCES:
         obj = out + "." + os.path.splitext(src)[0] + ".o"
         objs.append(obj)
-        procs.append((subprocess.Popen([_hipcc(), f"--offload-arch={ARCH}", *COMMON, "-c",
+        procs.append((subprocess.Popen([_hipcc(), f"--offload-arch={ARCH}", *COMMON,
+                                        *EXTRA.get(src, []), "-c",
                                         os.path.join(CSRC, src), "-o", obj]), src))
     failed = [src for p, src in procs if p.wait() != 0]
     if failed:

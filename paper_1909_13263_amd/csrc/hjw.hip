@@ -29,6 +29,7 @@
 #include "hjw.h"
 #include "hjw_common.h"
 #include "hjw_kernels.h"
+#include "hjw_resident.h"
 
 using namespace hjw;
 
@@ -83,6 +84,13 @@ struct hjw_grid {
     bool failed = false;
     DevState last{};
 
+    // the launch that holds the whole grid on the chip (hjw_resident.h); null ctl: none
+    ResidentArgs resident{};
+    int resident_ty = 0, resident_seg = 0;
+    bool use_resident = true;
+    char* exchange = nullptr;    // its mailboxes (a bound grid's; freed with it)
+    size_t exchange_bytes = 0;
+
     // graphs
     bool use_graph = true;
     hipGraphExec_t graph[2] = {nullptr, nullptr};   // by the parity the replay starts at
@@ -101,6 +109,114 @@ struct hjw_grid {
 };
 
 namespace {
+
+// The tile of the resident launch for this grid (hjw_resident.h): 0 where it has none.  A grid
+// takes the smallest tile that still gives at most one workgroup a compute unit, because its
+// step is then a chain of latencies (the march of a segment, the exchanges) and the shorter
+// segments and finishes are; one of more tiles takes 64 x 16, whose marches repeat the fewest
+// cells, as long as all fit: four of them a compute unit by LDS with the FP32 stencil, two in
+// FP64 (at three, of which some units then hold two, 768^2 took 57 us a step, launches per
+// stage 39).  us a step (Burgers, best of the launches per stage -> this launch):
+//   FP32 stencil  64^2 20.2 -> 13.2 (64 x 8: 14.6, 64 x 16: 17.6)   256^2 18.6 -> 12.8
+//                 320^2 18.3 -> 13.8 (64 x 4: 14.7)   512^2 19.0 -> 16.4 (64 x 8: 18.1)
+//                 640^2 23.8 -> 21.3   900^2 40.6 -> 35.5   1024^2 37.8 -> 30.4
+//   FP64          64^2 37.3 -> 18.7 (64 x 8: 23.2)   256^2 38.0 -> 19.3
+//                 400^2 36.0 -> 32.0   512^2 27.9 -> 21.6   640^2 32.2 -> 29.2
+constexpr int64_t kUnits = 256;   // compute units of the GPU this rule was measured on
+int resident_tile(const hjw_grid* g, int* seg, Split* sx, Split* sy) {
+    *seg = 1;
+    if (g->dim == 1) {
+        if (g->nx > int64_t(kMaxResident) * kResidentTX1) return 0;
+        *sx = split_axis(g->nx, kResidentTX1);
+        *sy = Split{1, 1, 0};
+        return 1;
+    }
+    const int64_t bx = (g->nx + kTX - 1) / kTX;
+    const struct { int ty, seg; int64_t most; } option[] = {
+        {4, 2, kUnits}, {8, 2, kUnits}, {16, 4, kUnits},
+        {16, 8, g->prec == HJW_FP64 ? 2 * kUnits : 4 * kUnits}};
+    for (const auto& o : option) {
+        if (bx * ((g->ny + o.ty - 1) / o.ty) > o.most) continue;
+        *seg = o.seg;
+        *sx = split_axis(g->nx, kTX);
+        *sy = split_axis(g->ny, o.ty);
+        return o.ty;
+    }
+    return 0;
+}
+
+template <typename T, typename P>
+size_t resident_layout(const hjw_grid* g, ResidentArgs* r, int* ty, int* seg, char* base) {
+    *ty = resident_tile(g, seg, &r->sx, &r->sy);
+    if (!*ty) return 0;
+    r->count = r->sx.nb * r->sy.nb;
+    r->remap = (g->dim == 2 && r->count % 8 == 0) ? 1 : 0;
+    const size_t elems = g->dim == 2 ? size_t(6 * (kTX + *ty)) : 6;
+    size_t o = 0;
+    const auto part = [&](unsigned long long** p, size_t words) {
+        *p = base ? reinterpret_cast<unsigned long long*>(base + o) : nullptr;
+        o += align256(words * 8);
+    };
+    unsigned long long* ctl = nullptr;
+    part(&ctl, sizeof(ResidentCtl) / 8);
+    r->ctl = reinterpret_cast<ResidentCtl*>(ctl);
+    part(&r->ranges, size_t(2) * range_words<T>() * r->count);
+    part(&r->groups, r->count <= kGroup ? 0
+                                        : size_t(2) * range_words<T>() * (kMaxResident / kGroup) *
+                                              (kMaxResident / kGroup));
+    part(&r->flux_mail, r->count * elems * TaggedFlux<T>::kWords);
+    part(&r->mid_mail, r->count * elems * Tagged<P>::kWords);
+    part(&r->last_mail, r->count * elems * Tagged<P>::kWords);
+    return o;
+}
+
+// The exchange area of the grid's resident launch: its size (0: the grid has none) and, with
+// base given, its parts.
+size_t resident_area(const hjw_grid* g, ResidentArgs* r, int* ty, int* seg, char* base) {
+    switch (g->prec) {
+    case HJW_FP64:
+        return resident_layout<double, double>(g, r, ty, seg, base);
+    case HJW_FP32_MIXED:
+        return resident_layout<float, double>(g, r, ty, seg, base);
+    default:
+        return resident_layout<float, float>(g, r, ty, seg, base);
+    }
+}
+
+// Take `bytes` at base as the grid's exchange area: no word carries a tag yet.
+hipError_t resident_bind(hjw_grid* g, char* base, size_t bytes) {
+    g->resident = ResidentArgs{};
+    if (!bytes) return hipSuccess;
+    resident_area(g, &g->resident, &g->resident_ty, &g->resident_seg, base);
+    g->resident.epoch = 1;
+    const int64_t words = int64_t(bytes / 8);
+    hipLaunchKernelGGL(k_clear_words, dim3(unsigned(std::min<int64_t>((words + 255) / 256, 1024))),
+                       dim3(256), 0, g->stream, reinterpret_cast<unsigned long long*>(base), words);
+    return hipGetLastError();
+}
+
+// A bound grid's exchange area, of its own (it is up to 51 bytes a node on small tiles, more
+// than the caller's workspace has to spare): none where the device has no room for it, and
+// the grid then steps with the launches per stage.
+void resident_free(hjw_grid* g) {
+    if (g->exchange) (void)hipFree(g->exchange);
+    g->exchange = nullptr;
+    g->resident = ResidentArgs{};
+}
+hipError_t resident_alloc(hjw_grid* g) {
+    ResidentArgs r{};
+    int ty, seg;
+    const size_t bytes = resident_area(g, &r, &ty, &seg, nullptr);
+    if (bytes != g->exchange_bytes) resident_free(g);
+    g->exchange_bytes = bytes;
+    if (bytes && !g->exchange &&
+        hipMalloc(reinterpret_cast<void**>(&g->exchange), bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        g->exchange = nullptr;
+        return hipSuccess;
+    }
+    return resident_bind(g, g->exchange, bytes);
+}
 
 void layout(const hjw_grid* g, size_t* off_phi2, size_t* off_flux, size_t* off_part,
             size_t* off_state, size_t* total, int* nbx, int* nby) {
@@ -338,6 +454,62 @@ hjw_status enqueue_steps(hjw_grid* g, int64_t n) {
     return HJW_OK;
 }
 
+// ------------------------------------------------------------------ the resident launch
+// Steps of one launch at most: other streams' work gets the GPU in between.
+constexpr int kResidentSteps = 256;
+
+const void* resident_kernel(const hjw_grid* g) {
+    return hjw::resident_kernel(g->prec, g->dim, g->resident_ty, g->resident_seg,
+                                g->ham == HJW_H_TIMED || g->llf);
+}
+int resident_threads(const hjw_grid* g) {
+    return g->dim == 1 ? kResidentTX1 : threads2d(g->resident_ty, g->resident_seg);
+}
+
+// Whether the grid's steps can go through the resident launch: default options, a family
+// whose stencil is plus-shaped, and room on this GPU for all its workgroups at once.
+bool resident_ready(const hjw_grid* g) {
+    if (!g->resident.ctl || !g->use_resident || g->timing || g->ham == HJW_H_CURVATURE) return false;
+    if (g->tile_rows != 16 || g->seg_opt || g->plan_opt) return false;
+    int dev = 0, cus = 0, per_cu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel(g),
+                                                     resident_threads(g), 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return int64_t(cus) * per_cu >= g->resident.count;
+}
+
+template <typename T, typename P>
+hipError_t launch_resident(const hjw_grid* g, ResidentArgs r) {
+    StageArgs<T, P> a = make_args<T, P>(g);
+    void* args[] = {&a, &r};
+    return hipLaunchKernel(resident_kernel(g), dim3(unsigned(r.count)),
+                           dim3(unsigned(resident_threads(g))), args, 0, g->stream);
+}
+
+// Up to `steps` steps in one launch.  With `set`, the step target goes to the device first.
+hipError_t enqueue_resident(const hjw_grid* g, int64_t steps, bool set, double t_final, double cfl,
+                            int64_t limit) {
+    ResidentArgs r = g->resident;
+    r.state = g->state;
+    r.max_steps = int(std::min<int64_t>(steps, kResidentSteps));
+    hipLaunchKernelGGL(k_resident_begin, dim3(1), dim3(64), 0, g->stream, g->state + g->par, r.ctl,
+                       set ? 1 : 0, t_final, cfl, limit);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    switch (g->prec) {
+    case HJW_FP64:
+        return launch_resident<double, double>(g, r);
+    case HJW_FP32_MIXED:
+        return launch_resident<float, double>(g, r);
+    default:
+        return launch_resident<float, float>(g, r);
+    }
+}
+
 hjw_status read_state(hjw_grid* g) {
     // the pinned mirror of a bound grid; the no-allocation solve has none and copies into
     // ordinary host memory
@@ -477,6 +649,7 @@ hjw_status hjw_bind(hjw_grid* g, void* ws, size_t bytes, void* stream) {
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(64), 0, g->stream, g->state,
                        static_cast<RangeSlots*>(g->slots));
     HIP_TRY(hipGetLastError());
+    HIP_TRY(resident_alloc(g));
     HIP_TRY(hipStreamSynchronize(g->stream));
     g->last = DevState{};
     return HJW_OK;
@@ -560,12 +733,33 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
     if (!std::isfinite(t_final) || !(cfl > 0.0) || !std::isfinite(cfl))
         return fail(HJW_EINVAL, "need finite t_final and cfl > 0");
     const int64_t limit = max_steps > 0 ? max_steps : std::numeric_limits<int64_t>::max();
-    hipLaunchKernelGGL(k_set_target, dim3(1), dim3(64), 0, g->stream, g->state + g->par, t_final, cfl,
-                       limit);
-    HIP_TRY(hipGetLastError());
-    s = read_state(g);
-    if (s != HJW_OK) return s;
     int64_t taken = 0;
+    bool set = true;   // the step target has still to be set
+    // The host's mirror of the record is current between calls.
+    while (g->last.t < t_final && taken < limit && !g->last.bad && resident_ready(g)) {
+        HIP_TRY(enqueue_resident(g, limit - taken, set, t_final, cfl, limit));
+        set = false;
+        const int64_t before = g->last.steps;
+        s = read_state(g);
+        if (s != HJW_OK) return s;
+        if (g->last.pad[0] == 0) break;   // its workgroups did not come together: step by stages
+        if (g->last.pad[0] == 2) {
+            g->failed = true;
+            return fail(HJW_EHIP, "a workgroup stopped answering at step %lld",
+                        (long long)g->last.steps);
+        }
+        const int64_t steps = g->last.steps - before;
+        g->resident.epoch += unsigned(steps) + 1u;
+        taken += steps;
+        if (steps == 0 && !g->last.bad) break;
+    }
+    if (set) {
+        hipLaunchKernelGGL(k_set_target, dim3(1), dim3(64), 0, g->stream, g->state + g->par,
+                           t_final, cfl, limit);
+        HIP_TRY(hipGetLastError());
+        s = read_state(g);
+        if (s != HJW_OK) return s;
+    }
     while (g->last.t < t_final && taken < limit && !g->last.bad) {
         // Steps enqueued before the next read of the step state: one graph's worth
         // while dt is unknown, else the estimate from the last dt plus a margin (dt
@@ -644,6 +838,7 @@ hjw_status hjw_set_option(hjw_grid* g, int option, int64_t value) {
     if (!g) return fail(HJW_EINVAL, "grid is NULL");
     if (option == HJW_OPT_USE_GRAPH) {
         g->use_graph = value != 0;
+        g->use_resident = value != 0;   // launch by launch, as asked
         if (!g->use_graph) drop_graph(g);
         return HJW_OK;
     }
@@ -777,6 +972,7 @@ void hjw_grid_destroy(hjw_grid* g) {
     for (auto& e : g->ev)
         if (e) (void)hipEventDestroy(e);
     if (g->stream) (void)hipStreamSynchronize(g->stream);
+    resident_free(g);
     if (g->own_stream && g->stream) (void)hipStreamDestroy(g->stream);
     if (g->pinned) (void)hipHostFree(g->pinned);
     delete g;
@@ -796,7 +992,12 @@ namespace {
 constexpr int64_t kNoAllocNodes = int64_t(1) << 20;   // e.g. a 1024 x 1024 grid
 constexpr size_t kNoAllocControl = 4096;               // range slots and step records
 // FP64 is the largest case: stage buffer 8 B and flux records 24 B per node.
-constexpr size_t kNoAllocBytes = size_t(kNoAllocNodes) * 32 + kNoAllocControl;
+// The exchange area of a resident launch: mailboxes of at most 1024 tiles of 64 x 16 FP64 nodes
+// (480 elements of 8 words) and the reductions' words.
+constexpr size_t kNoAllocExchange =
+    size_t(kMaxResident) * (mail_words<double, double>(6 * (kTX + 16)) + 2 * range_words<double>()) * 8 +
+    2 * range_words<double>() * (kMaxResident / kGroup) * (kMaxResident / kGroup) * 8 + 16384;
+constexpr size_t kNoAllocBytes = size_t(kNoAllocNodes) * 32 + kNoAllocControl + kNoAllocExchange;
 static_assert(align256(sizeof(RangeSlots)) + align256(2 * sizeof(DevState)) <= kNoAllocControl,
               "control records fit");
 
@@ -873,6 +1074,10 @@ hjw_status hjw_solve_noalloc(int dim, const int64_t* n, const double* lo, const 
     g.stream = static_cast<hipStream_t>(stream);
     g.use_graph = false;   // instantiating a graph allocates
     g.bound = true;
+    ResidentArgs r_{};
+    int ty_, seg_;
+    const size_t exchange = resident_area(&g, &r_, &ty_, &seg_, nullptr);
+    if (o + exchange <= kNoAllocBytes) HIP_TRY(resident_bind(&g, base + o, exchange));
 
     // phi0: reset the step records and range slots (the array keeps the last call's
     // contents), check it, and convert it to FP32 storage where phi is stored so

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "hjw_tile.h"
+#include "hjw_resident.h"
 
 using namespace hjw;
 
@@ -297,9 +298,251 @@ int step(const Problem& pr, double* phi, double t, double t_final, double cfl, d
     return e.guards() ? 0 : -7;
 }
 
+// The resident launch: the same borders, mailboxes and finishes, every tile's phase before any
+// tile's next one.  The mailboxes lie between guard zones, and a word that should have come
+// but does not carry the step's tag ends the run.
+struct Words {
+    std::vector<u64> buf;
+    size_t n;
+    static constexpr u64 kMark = 0xdeadbeefdeadbeefull;
+    explicit Words(size_t n_) : buf(n_ + 2 * kGuard, kMark), n(n_) {
+        std::fill(buf.begin() + kGuard, buf.begin() + kGuard + n, 0ull);
+    }
+    u64* data() { return buf.data() + kGuard; }
+    bool intact() const {
+        for (size_t k = 0; k < kGuard; ++k)
+            if (buf[k] != kMark || buf[kGuard + n + k] != kMark) return false;
+        return true;
+    }
+};
+
+template <typename T, typename P, int TX, int TY, int S>
+struct EmuResident {
+    static constexpr bool k2D = TY > 1;
+    using TL2 = Tile<T, P, kTX, k2D ? TY : 16, k2D ? S : 8, k2D ? S : 8>;
+    using TL1 = Tile1D<T, P, kResidentTX1, 1>;
+    static constexpr int kThreads = k2D ? TL2::kThreads : TL1::kThreads;
+    static constexpr int kPhi = k2D ? TL2::kPhiElems : TL1::kPhiElems;
+    static constexpr int kU = k2D ? TL2::kUElems : TL1::kUElems;
+    using RT = ResidentTile<T, P, k2D ? TY : 16, k2D ? S : 8>;
+    using BD = Border<T, P, TX, TY, k2D ? TL2::PW : TL1::PW, k2D ? 2 : 1, kThreads>;
+
+    struct TileState {
+        Spot s;
+        std::vector<P> phiL, pn;
+        std::vector<T> uL, vL;
+        std::vector<Flux3<T>> fl;
+    };
+    Emu<T, P>& e;
+    StageArgs<T, P> a;
+    ResidentArgs r{};
+    std::vector<TileState> tiles;
+    Words flux, mid, last;
+
+    EmuResident(Emu<T, P>& e_, Split sx, Split sy)
+        : e(e_), a(e_.args()), flux(size_t(sx.nb) * sy.nb * BD::kElems * TaggedFlux<T>::kWords),
+          mid(size_t(sx.nb) * sy.nb * BD::kElems * Tagged<P>::kWords),
+          last(size_t(sx.nb) * sy.nb * BD::kElems * Tagged<P>::kWords) {
+        r.sx = sx;
+        r.sy = sy;
+        r.count = sx.nb * sy.nb;
+        tiles.resize(size_t(r.count));
+        for (int k = 0; k < r.count; ++k) {
+            TileState& ts = tiles[size_t(k)];
+            ts.s = make_spot(r, k, a.dim, a.bcx, a.bcy);
+            ts.phiL.assign(kPhi, P(NAN));
+            for (int t = 0; t < kThreads; ++t)
+                BD::template load<kPhi>(t, ts.s, a, ts.phiL.data());
+            ts.pn.resize(size_t(TX) * TY);
+            ts.fl.resize(size_t(TX) * TY);
+            for (int j = 0; j < ts.s.h; ++j)
+                for (int i = 0; i < ts.s.w; ++i) ts.pn[size_t(j) * TX + i] = ts.phiL[BD::own(i, j)];
+        }
+    }
+    void sweeps(TileState& ts) {
+        ts.uL.assign(kU, T(NAN));
+        if constexpr (k2D) {
+            ts.vL.assign(RT::kVElems, T(NAN));
+            for (int t = 0; t < TL2::kHalf; ++t) TL2::sweep_x(t, a, ts.phiL.data(), ts.uL.data());
+            for (int t = 0; t < TL2::kHalf; ++t) RT::sweep_y(t, a, ts.phiL.data(), ts.vL.data());
+        } else {
+            for (int t = 0; t < kThreads; ++t) TL1::sweep_x(t, a, ts.phiL.data(), ts.uL.data());
+        }
+    }
+    static Flux3<T> flux_of(const TileState& ts, int c, int j) {
+        if constexpr (k2D)
+            return RT::get_flux(ts.uL.data(), ts.vL.data(), c, j);
+        else
+            return ts.fl[size_t(c)];
+    }
+    template <class Fin, class Hand>
+    void finish(TileState& ts, Fin& fin, Hand hand) {
+        fin.room_x = ts.s.w;
+        fin.room_y = k2D ? ts.s.h : 1;
+        if constexpr (k2D) {
+            const auto nodes = [&](auto mode) {
+                for (int j = 0; j < ts.s.h; ++j)
+                    for (int c = 0; c < ts.s.w; ++c) {
+                        RT::template node<decltype(mode)::value>(
+                            fin, c, j, ts.uL.data(), ts.vL.data(), ts.phiL[BD::own(c, j)],
+                            ts.pn[size_t(j) * TX + c]);
+                        hand(c, j, fin.sink);
+                    }
+            };
+            const int mode = fin.mode();
+            if (mode == kNodeTimed) nodes(std::integral_constant<int, kNodeTimed>{});
+            else if (mode == kNodeExtended) nodes(std::integral_constant<int, kNodeExtended>{});
+            else nodes(std::integral_constant<int, kNodePlain>{});
+        } else {
+            for (int c = 0; c < ts.s.w; ++c) {
+                fin(c, 0, ts.uL[c], ts.uL[kResidentTX1 + c], T(0), T(0), ts.phiL[c + 3], ts.pn[c]);
+                hand(c, 0, fin.sink);
+            }
+        }
+    }
+    template <class Rec, class Use>
+    bool receive(TileState& ts, const u64* mail, unsigned int tag, Use use) {
+        bool ok = true;
+        for (int t = 0; t < kThreads; ++t) {
+            typename BD::template Received<Rec, BD::kRounds> g;
+            BD::expect(t, kThreads, ts.s, g);
+            ok = BD::look(t, kThreads, ts.s, tag, mail, g) && ok;
+            for (int k = 0; k < BD::kRounds; ++k)
+                if (g.at[k] >= 0) use(ts.phiL[g.at[k]], g.rec[k].value());
+        }
+        return ok;
+    }
+    void settle(TileState& ts) {
+        // every own node and received halo value is in place on all tiles: own first
+        if (ts.s.any_local)
+            for (int t = 0; t < kThreads; ++t) BD::fill_local(t, ts.s, a, ts.phiL.data());
+    }
+
+    // Steps until t_final or `steps`; 0 done, -5 non-finite, -6 a word missing.
+    int run(DevState& st, int steps) {
+        for (int step = 0; step < steps && !st.bad && st.t < st.t_final; ++step) {
+            const unsigned int tag = 65530u + unsigned(step);   // crosses the 16-bit tags' end
+            DevState tn = st;
+            a.st = &tn;
+            a.par = 0;
+            double box[4] = {INFINITY, -INFINITY, INFINITY, -INFINITY};
+            bool bad = false, ok = true;
+            for (TileState& ts : tiles) {
+                sweeps(ts);
+                Finisher<kStagePre, T, P, true, Kept<T, P>> fin(a, ts.s.x0, ts.s.y0, 0, 0, 0, a.dim);
+                finish(ts, fin, [&](int c, int j, const Kept<T, P>& k) {
+                    if constexpr (k2D)
+                        RT::put_flux(ts.uL.data(), ts.vL.data(), c, j, k.f);
+                    else
+                        ts.fl[size_t(c)] = k.f;
+                });
+                for (int t = 0; t < kThreads; ++t)
+                    BD::send_flux(t, kThreads, ts.s, [&](int c, int j) { return flux_of(ts, c, j); },
+                                  tag, flux.data());
+                box[0] = std::fmin(box[0], double(fin.lo_u));
+                box[1] = std::fmax(box[1], double(fin.hi_u));
+                box[2] = std::fmin(box[2], double(k2D ? fin.lo_v : T(0)));
+                box[3] = std::fmax(box[3], double(k2D ? fin.hi_v : T(0)));
+                bad = bad || fin.bad;
+            }
+            if (bad) return -5;
+            plan_step(st, a.ham, a.hpD, a.dim, 1.0 / e.pr.dx, a.dim == 2 ? 1.0 / e.pr.dy : 0.0, box);
+            if (st.bad) return -5;
+            const double dt = st.dt, ax = st.alpha_x, ay = st.alpha_y;
+            for (TileState& ts : tiles) {
+                ok = receive<TaggedFlux<T>>(ts, flux.data(), tag, [&](P& v, const Flux3<T>& f) {
+                         v = BD::phi1(v, f, dt, ax, ay);
+                     }) && ok;
+                for (int j = 0; j < ts.s.h; ++j)
+                    for (int c = 0; c < ts.s.w; ++c)
+                        ts.phiL[BD::own(c, j)] = BD::phi1(ts.pn[size_t(j) * TX + c],
+                                                          flux_of(ts, c, j), dt, ax, ay);
+                settle(ts);
+            }
+            for (TileState& ts : tiles) {
+                sweeps(ts);
+                Finisher<kStageMid, T, P, true, Kept<T, P>> fin(a, ts.s.x0, ts.s.y0, dt, ax, ay, a.dim);
+                finish(ts, fin, [&](int c, int j, const Kept<T, P>& k) {
+                    ts.phiL[BD::own(c, j)] = k.v;
+                });
+                for (int t = 0; t < kThreads; ++t)
+                    BD::send_phi(t, kThreads, ts.s, ts.phiL.data(), tag, mid.data());
+            }
+            for (TileState& ts : tiles) {
+                ok = receive<Tagged<P>>(ts, mid.data(), tag, [](P& v, P x) { v = x; }) && ok;
+                settle(ts);
+            }
+            for (TileState& ts : tiles) {
+                sweeps(ts);
+                Finisher<kStageLast, T, P, true, Kept<T, P>> fin(a, ts.s.x0, ts.s.y0, dt, ax, ay, a.dim);
+                finish(ts, fin, [&](int c, int j, const Kept<T, P>& k) {
+                    ts.phiL[BD::own(c, j)] = ts.pn[size_t(j) * TX + c] = k.v;
+                });
+                for (int t = 0; t < kThreads; ++t)
+                    BD::send_phi(t, kThreads, ts.s, ts.phiL.data(), tag, last.data());
+                if (fin.bad) st.bad = 1;
+            }
+            for (TileState& ts : tiles) {
+                ok = receive<Tagged<P>>(ts, last.data(), tag, [](P& v, P x) { v = x; }) && ok;
+                settle(ts);
+            }
+            if (!ok) return -6;
+        }
+        for (TileState& ts : tiles)
+            for (int j = 0; j < ts.s.h; ++j)
+                for (int c = 0; c < ts.s.w; ++c)
+                    e.phi.data()[(ts.s.y0 + j) * a.nx + ts.s.x0 + c] = ts.pn[size_t(j) * TX + c];
+        if (!flux.intact() || !mid.intact() || !last.intact()) return -7;
+        return st.bad ? -5 : 0;
+    }
+};
+
+template <typename T, typename P, int TX, int TY, int S>
+int resident_run(Emu<T, P>& e, DevState& st, int steps) {
+    EmuResident<T, P, TX, TY, S> x(e, split_axis(e.pr.nx, TX),
+                                   TY > 1 ? split_axis(e.pr.ny, TY) : Split{1, 1, 0});
+    return x.run(st, steps);
+}
+
+template <typename T, typename P>
+int resident(const Problem& pr, double* phi, double t, double t_final, double cfl, int steps, int ty,
+             int seg, double* info) {
+    Emu<T, P> e(pr);
+    for (size_t k = 0; k < e.n; ++k) e.phi.data()[k] = P(phi[k]);
+    DevState st{};
+    st.t = t;
+    st.t_final = t_final;
+    st.cfl = cfl;
+    st.steps_left = steps;
+    int rc = -1;
+    if (pr.dim == 1) rc = resident_run<T, P, kResidentTX1, 1, 1>(e, st, steps);
+    else if (ty == 8 && seg == 2) rc = resident_run<T, P, kTX, 8, 2>(e, st, steps);
+    else if (ty == 4 && seg == 2) rc = resident_run<T, P, kTX, 4, 2>(e, st, steps);
+    else if (ty == 16 && seg == 4) rc = resident_run<T, P, kTX, 16, 4>(e, st, steps);
+    else if (ty == 16 && seg == 8) rc = resident_run<T, P, kTX, 16, 8>(e, st, steps);
+    for (size_t k = 0; k < e.n; ++k) phi[k] = double(e.phi.data()[k]);
+    info[0] = st.t;
+    info[1] = st.dt;
+    info[2] = st.alpha_x;
+    info[3] = st.alpha_y;
+    for (int k = 0; k < 4; ++k) info[4 + k] = st.range[k];
+    info[8] = st.bad ? 1.0 : 0.0;
+    return e.guards() ? rc : -7;
+}
+
 }  // namespace
 
 extern "C" {
+
+// Up to `steps` steps of the resident launch's tiles (2-D: 64 x ty nodes, segments of seg).
+int hjw_emu_resident(int dim, int64_t nx, int64_t ny, double dx, double dy, int bcx, int bcy,
+                     int prec, int ham, const double* hp, double* phi, double t, double t_final,
+                     double cfl, int steps, int ty, int seg, double* info) {
+    const Problem p = make_problem(dim, nx, ny, dx, dy, bcx, bcy, ham, hp);
+    if (prec == 0) return resident<double, double>(p, phi, t, t_final, cfl, steps, ty, seg, info);
+    if (prec == 1) return resident<float, double>(p, phi, t, t_final, cfl, steps, ty, seg, info);
+    return resident<float, float>(p, phi, t, t_final, cfl, steps, ty, seg, info);
+}
 
 // Height of the emulated 2-D tile (32 or 16), as HJW_OPT_TILE_ROWS selects on the GPU.
 int hjw_emu_set_tile_rows(int rows) {

@@ -1104,11 +1104,26 @@ struct Tile1D {
 
 // ---------------------------------------------------------------- node finish
 
+// What a node's finish hands on goes to the grid's arrays: its flux record (first stage) or
+// its phi, in the row that starts at rbase.
+struct ToGrid {
+    template <typename T, typename P>
+    __host__ __device__ static void flux(const StageArgs<T, P>& a, int64_t rbase, uint32_t col,
+                                         const Flux3<T>& rec) {
+        at(reinterpret_cast<Flux3<T>*>(a.flux) + rbase, col) = rec;
+    }
+    template <typename T, typename P>
+    __host__ __device__ static void phi(const StageArgs<T, P>& a, int64_t rbase, uint32_t col,
+                                        P v) {
+        at(a.out + rbase, col) = v;
+    }
+};
+
 // Per-node work after both sweeps, for each stage kind.  Holds running
 // min/max of the derivatives for the pre-stage.
 // TIMED: the launch may carry the time- and phi-dependent family (its code is compiled
 // only into kernels that take it, so that it does not change the others' code).
-template <int STAGE, typename T, typename P, bool TIMED>
+template <int STAGE, typename T, typename P, bool TIMED, class Sink = ToGrid>
 struct Finisher {
     static constexpr bool kTimed = TIMED;
     // the second and third stages read phi^n at the node (a compile-time fact: an LDS
@@ -1126,6 +1141,7 @@ struct Finisher {
     const P* tileL = nullptr;   // the stage input on the tile (2-D; curvature term only)
     int pw = 0;                 // its row pitch
     T cos_wt = T(0);            // TIMED: cos(w t) at this stage's time
+    Sink sink;                  // where the node's results go
 
     __host__ __device__ Finisher(const StageArgs<T, P>& args, int64_t x0_, int64_t y0_,
                                  double dt_, double ax_, double ay_, int dim_)
@@ -1220,7 +1236,7 @@ struct Finisher {
         const bool hold = EXT && held(i, j);
         if (STAGE == kStagePre && hold) {
             // phi_1 = phi^n - dt (0 - 0) is phi^n exactly
-            at(reinterpret_cast<Flux3<T>*>(a.flux) + rbase, ucol) = Flux3<T>{T(0), T(0), T(0)};
+            sink.flux(a, rbase, ucol, Flux3<T>{T(0), T(0), T(0)});
             return;
         }
         const T ub = T(0.5) * (up + um), vb = T(0.5) * (vp + vm);
@@ -1249,9 +1265,9 @@ struct Finisher {
             // alpha is known here: the record holds the whole numerical Hamiltonian (the
             // second stage subtracts the global alpha times zero)
             const double r = double(H) - (mul_rn(lax, double(Dx)) + mul_rn(lay, double(Dy)));
-            at(reinterpret_cast<Flux3<T>*>(a.flux) + rbase, ucol) = Flux3<T>{T(r), T(0), T(0)};
+            sink.flux(a, rbase, ucol, Flux3<T>{T(r), T(0), T(0)});
         } else if (STAGE == kStagePre) {
-            at(reinterpret_cast<Flux3<T>*>(a.flux) + rbase, ucol) = Flux3<T>{H, Dx, Dy};
+            sink.flux(a, rbase, ucol, Flux3<T>{H, Dx, Dy});
         }
         if (STAGE == kStagePre) {
             lo_u = fmin(lo_u, fmin(um, up));
@@ -1276,7 +1292,7 @@ struct Finisher {
             res = fma(1.0 / 3.0, pn, mul_rn(2.0 / 3.0, euler));
         }
         const P outv = EXT && hold ? pn_ : P(res);
-        at(a.out + rbase, ucol) = outv;
+        sink.phi(a, rbase, ucol, outv);
         bad |= !finite_t(outv);
     }
 };

@@ -34,6 +34,10 @@ def lib():
         L.hjw_emu_step.restype = ctypes.c_int
         L.hjw_emu_step.argtypes = [ctypes.c_int, i64, i64, d, d, ctypes.c_int, ctypes.c_int,
                                    ctypes.c_int, ctypes.c_int, vp, vp, d, d, d, vp]
+        L.hjw_emu_resident.restype = ctypes.c_int
+        L.hjw_emu_resident.argtypes = [ctypes.c_int, i64, i64, d, d, ctypes.c_int, ctypes.c_int,
+                                       ctypes.c_int, ctypes.c_int, vp, vp, d, d, d, ctypes.c_int,
+                                       ctypes.c_int, ctypes.c_int, vp]
         _lib = L
     return _lib
 
@@ -94,4 +98,16 @@ def rk3_step(phi, h, ham, params, t, t_final, cfl, bc=0, prec=0):
     info = np.zeros(9)
     rc = lib().hjw_emu_step(dim, nx, ny, dx, dy, bx, by, prec, ham, _p(hp), _p(out), t,
                             t_final, cfl, _p(info))
+    return rc, out, info
+
+
+def resident_steps(phi, h, ham, params, t, t_final, cfl, steps, tile, bc=0, prec=0):
+    """Up to `steps` steps of the resident launch's tiles; tile = (rows, segment) in 2-D."""
+    out = np.array(phi, dtype=np.float64, copy=True, order="C")
+    dim, nx, ny, dx, dy, bx, by = _geom(out.shape, h, bc)
+    hp = np.zeros(4)
+    hp[:len(params)] = params
+    info = np.zeros(9)
+    rc = lib().hjw_emu_resident(dim, nx, ny, dx, dy, bx, by, prec, ham, _p(hp), _p(out), t,
+                                t_final, cfl, int(steps), tile[0], tile[1], _p(info))
     return rc, out, info
