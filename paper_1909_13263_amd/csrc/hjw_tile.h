@@ -255,11 +255,11 @@ template <> struct SeriesCfg<float> { static constexpr float tau2 = 1.0e-2f; };
 //   2M = sqrt(q4) X,  X = 1 + g^2 (2/3 + g^2 (2/5 (sg^2-1) + g^2 2/7 (sg^4 - 6 sg^2 + 2))),
 //   q4 = 4 + sg^2, g = dl / q4
 // (the Taylor series of the mean about m = sg/2 with y = (h/(1+m^2))^2 = 4 g^2), so
-// (2M)^2 = q4 X^2 needs no square root.  xx receives the squared relative gap dl^2 / q4.
-__host__ __device__ inline double mean2sq_series(double sg, double dl, double q4, double& xx) {
-    // g enters X only through g^2 <= tau2 / q4 <= 1e-4 wherever the series is used, so the
-    // reciprocal's error, below 2^-46, stays far below the rounding of X
-    const double g = dl * rcp_once(q4);
+// (2M)^2 = q4 X^2 needs no square root.
+// r is 1/q4; xx receives the squared relative gap.
+__host__ __device__ inline double mean2sq_series(double sg, double dl, double q4, double r,
+                                                 double& xx) {
+    const double g = dl * r;
     xx = dl * g;
     const double g2 = g * g;
     const double s2 = mul_rn(sg, sg);
@@ -268,8 +268,8 @@ __host__ __device__ inline double mean2sq_series(double sg, double dl, double q4
     const double X = fma_t(g2, inner, 1.0);
     return mul_rn(q4 * X, X);   // rounded alone: the weights add eps to it on every path
 }
-__host__ __device__ inline float mean2sq_series(float sg, float dl, float q4, float& xx) {
-    const float g = dl * rcp_t(q4);
+__host__ __device__ inline float mean2sq_series(float sg, float dl, float q4, float r, float& xx) {
+    const float g = dl * r;
     xx = dl * g;
     const float g2 = g * g;
     const float inner = fma_t(g2, 0.4f * fma_t(sg, sg, -1.0f), 2.0f / 3.0f);
@@ -310,6 +310,36 @@ __host__ __device__ inline float add_quot(float q, float num, float den) {
     return fma_t(num, rcp_t(den), q);
 }
 
+// 1/qA, 1/qB, 1/qC.  FP64: from one reciprocal of the product (a reciprocal takes four times
+// an FMA's issue; the product of three is in range as long as the weights' products of four
+// are).  The gaps' quotients enter the series only through g^2 <= tau2 / q4 <= 1e-4 wherever it
+// is used, so the error of one Newton step and six products, below 1e-14, stays far below
+// the rounding of X.
+__host__ __device__ inline void recip3(double qA, double qB, double qC, double& rA, double& rB,
+                                       double& rC) {
+    const double qAB = mul_rn(qA, qB);
+    const double r = rcp_once(mul_rn(qAB, qC));
+    rC = mul_rn(r, qAB);
+    const double rAB = mul_rn(r, qC);
+    rA = mul_rn(rAB, qB);
+    rB = mul_rn(rAB, qA);
+}
+__host__ __device__ inline void recip3(float qA, float qB, float qC, float& rA, float& rB,
+                                       float& rC) {
+    rA = rcp_t(qA);
+    rB = rcp_t(qB);
+    rC = rcp_t(qC);
+}
+
+// The antiderivative at a cell's left end value c0 (the previous cell's c1), where the march
+// has it: every cell of a kinked stretch takes the wide branch, and one of its four
+// antiderivatives is the previous cell's.
+template <typename T>
+struct EndValue {
+    T p = T(0);
+    bool known = false;   // uniform over the wave
+};
+
 // Squares of the doubled means for the three pairs of one cell: (c0, b1), (c0, c1),
 // (f0, c1).  A pair whose relative half-gap is not small takes the antiderivative
 // instead; the wave takes that branch only when one of its lanes needs it.  The
@@ -317,31 +347,41 @@ __host__ __device__ inline float add_quot(float q, float num, float den) {
 // on whether its wave took the branch (a product fused into the weights' sums on one
 // path only would round differently).
 template <typename T>
-__host__ __device__ inline void cell_means(T c0, T b1, T c1, T f0, T& MA2, T& MB2, T& MC2) {
+__host__ __device__ inline void cell_means(T c0, T b1, T c1, T f0, T& MA2, T& MB2, T& MC2,
+                                           EndValue<T>& end) {
     const T tau2 = SeriesCfg<T>::tau2;
     const T sA = c0 + b1, dA = b1 - c0;
     const T sB = c0 + c1, dB = c1 - c0;
     const T sC = f0 + c1, dC = c1 - f0;
     const T qA = fma_t(sA, sA, T(4)), qB = fma_t(sB, sB, T(4)), qC = fma_t(sC, sC, T(4));
     // half-gap dl/2 against tau sqrt(1 + m^2) = tau sqrt(q4)/2: wide when dl^2/q4 >= tau^2
-    T xA, xB, xC;
-    MA2 = mean2sq_series(sA, dA, qA, xA);
-    MB2 = mean2sq_series(sB, dB, qB, xB);
-    MC2 = mean2sq_series(sC, dC, qC, xC);
+    T rA, rB, rC, xA, xB, xC;
+    recip3(qA, qB, qC, rA, rB, rC);
+    MA2 = mean2sq_series(sA, dA, qA, rA, xA);
+    MB2 = mean2sq_series(sB, dB, qB, rB, xB);
+    MC2 = mean2sq_series(sC, dC, qC, rC, xC);
     if (any_lane(fmax(xA, fmax(xB, xC)) >= tau2)) {
-        const T Pc0 = prim(c0), Pb1 = prim(b1), Pc1 = prim(c1), Pf0 = prim(f0);
-        if (xA >= tau2) {
-            const T M = wdiv(T(2) * (Pb1 - Pc0), dA);
-            MA2 = mul_rn(M, M);
+        // only the antiderivatives of pairs that are wide on some lane (uniform tests)
+        const bool wA = any_lane(xA >= tau2), wB = any_lane(xB >= tau2), wC = any_lane(xC >= tau2);
+        T P0 = end.p, P1 = T(0);
+        if ((wA || wB) && !end.known) P0 = prim(c0);
+        end.known = wB || wC;
+        if (end.known) P1 = prim(c1);
+        end.p = P1;
+        if (wA) {
+            const T M = wdiv(T(2) * (prim(b1) - P0), dA);
+            MA2 = xA >= tau2 ? mul_rn(M, M) : MA2;
         }
-        if (xB >= tau2) {
-            const T M = wdiv(T(2) * (Pc1 - Pc0), dB);
-            MB2 = mul_rn(M, M);
+        if (wB) {
+            const T M = wdiv(T(2) * (P1 - P0), dB);
+            MB2 = xB >= tau2 ? mul_rn(M, M) : MB2;
         }
-        if (xC >= tau2) {
-            const T M = wdiv(T(2) * (Pc1 - Pf0), dC);
-            MC2 = mul_rn(M, M);
+        if (wC) {
+            const T M = wdiv(T(2) * (P1 - prim(f0)), dC);
+            MC2 = xC >= tau2 ? mul_rn(M, M) : MC2;
         }
+    } else {
+        end.known = false;
     }
 }
 
@@ -417,12 +457,13 @@ __host__ __device__ inline void sweep_emit(const P* line, int stride, P ihP, T i
     // product fused into a sum in one iteration but not in another would make a node's
     // value depend on where its segment starts.
     T c0 = mul_rn(e2, ih);
+    EndValue<T> end;
 #pragma unroll
     for (int it = 0; it <= S; ++it) {
         const T c = v[it + 2];
         const T e4 = v[it + 4] - v[it + 3];
-        const T B1 = T(2) * e2 - e1;          // h B_i
-        const T F0 = T(2) * e3 - e4;          // h F_{i-1}
+        const T B1 = fma_t(T(2), e2, -e1);    // h B_i
+        const T F0 = fma_t(T(2), e3, -e4);    // h F_{i-1}
         const T c1 = mul_rn(e3, ih);          // C_i
         const T b1 = mul_rn(B1, ih);          // B_i
         const T f0 = mul_rn(F0, ih);          // F_{i-1}
@@ -430,24 +471,25 @@ __host__ __device__ inline void sweep_emit(const P* line, int stride, P ihP, T i
         if (SCHEME == kSchemeJP)
             jp_indicators(e1, e2, e3, e4, XA, XB, XC);
         else
-            cell_means(c0, b1, c1, f0, XA, XB, XC);
+            cell_means(c0, b1, c1, f0, XA, XB, XC, end);
         T pAB, pAC, pBC;
         weight_products(XA, XB, XC, eps4, pAB, pAC, pBC);
         const T D3a = B1 - e3;                // a - 3b + 3c - d
         const T D3b = F0 - e2;                // b - 3c + 3d - e
-        // numerators and denominators below are six times those of the weighted sums
+        // numerators and denominators below are three times those of the weighted sums (the
+        // multiple that takes the fewest instructions; powers of two round alike)
         const T xa = mul_rn(pBC, D3a), xb = mul_rn(pAB, D3b);
-        const T p36AC = mul_rn(T(36), pAC);
+        const T p18AC = mul_rn(T(18), pAC);
         if (it < S) {  // phi^- at node i: weights (1/10, 6/10, 3/10) on (A, B, C)
-            const T q1 = fma_t(e2 + T(2) * e3, T(1.0 / 6.0), c);
-            const T num = fma_t(T(3), xb, xa + xa);             // 6 (pBC D3a/3 + pAB D3b/2)
-            const T den = fma_t(T(18), pAB, fma_t(T(6), pBC, p36AC));
+            const T q1 = fma_t(fma_t(T(2), e3, e2), T(1.0 / 6.0), c);
+            const T num = fma_t(T(1.5), xb, xa);                // 3 (pBC D3a/3 + pAB D3b/2)
+            const T den = fma_t(T(9), pAB, fma_t(T(3), pBC, p18AC));
             emit.minus(it, add_quot(q1, num, den));
         }
         if (it > 0) {  // phi^+ at node i-1: the mirrored sub-stencils, (1/10, 6/10, 3/10) on (C, B, A)
-            const T qp1 = fma_t(-(e3 + T(2) * e2), T(1.0 / 6.0), c);
-            const T num = fma_t(T(3), xa, xb + xb);             // 6 (pAB D3b/3 + pBC D3a/2)
-            const T den = fma_t(T(18), pBC, fma_t(T(6), pAB, p36AC));
+            const T qp1 = fma_t(-fma_t(T(2), e2, e3), T(1.0 / 6.0), c);
+            const T num = fma_t(T(1.5), xa, xb);                // 3 (pAB D3b/3 + pBC D3a/2)
+            const T den = fma_t(T(9), pBC, fma_t(T(3), pAB, p18AC));
             emit.plus(it - 1, add_quot(qp1, -num, den));
         }
         e1 = e2;
