@@ -110,6 +110,9 @@ struct hjw_grid {
 
 namespace {
 
+// Compute units of the GPU that the rules below were measured on.
+constexpr int kUnits = 256;
+
 // The tile of the resident launch for this grid (hjw_resident.h): 0 where it has none.  A grid
 // takes the smallest tile that still gives at most one workgroup a compute unit, because its
 // step is then a chain of latencies (the march of a segment, the exchanges) and the shorter
@@ -122,7 +125,6 @@ namespace {
 //                 640^2 23.8 -> 21.3   900^2 40.6 -> 35.5   1024^2 37.8 -> 30.4
 //   FP64          64^2 37.3 -> 18.7 (64 x 8: 23.2)   256^2 38.0 -> 19.3
 //                 400^2 36.0 -> 32.0   512^2 27.9 -> 21.6   640^2 32.2 -> 29.2
-constexpr int64_t kUnits = 256;   // compute units of the GPU this rule was measured on
 int resident_tile(const hjw_grid* g, int* seg, Split* sx, Split* sy) {
     *seg = 1;
     if (g->dim == 1) {
@@ -305,10 +307,21 @@ int segment(const hjw_grid* g) {
                                                                                           : 8;
 }
 
+// FP64 grids of more tiles than three a CU and at most four take the dense kernels, so that a
+// stage is one round of workgroups and not one and a fraction: 1024^2 61.5 -> 54.0 us a step, 900^2
+// 62.5 -> 54.6, level set 1024^2 100.6 -> 92.4.  With one round or several anyway they lose: 768^2
+// 38.4 -> 41.2, and beyond the cache, where phi^n read twice is memory traffic, 3000^2 345 -> 361,
+// 4096^2 597 -> 632.
+bool dense_tiles(const hjw_grid* g) {
+    const int tiles = g->nbx * g->nby;
+    return g->prec == HJW_FP64 && tiles > 3 * kUnits && tiles <= 4 * kUnits;
+}
+
 template <typename T, typename P, int STAGE>
 hipError_t launch_stage(const hjw_grid* g, StageArgs<T, P> a) {
     const dim3 grid(unsigned(g->nbx * g->nby));
     constexpr bool kNarrow = !std::is_same<T, double>::value;   // the S = 4 kernels
+    constexpr bool kDense = !kNarrow && STAGE != kStageDeriv;
     // the time- and phi-dependent family and the local dissipation have kernels of their
     // own (16-row tiles, 8-node segments), so that the other kernels carry none of their code
     constexpr bool kH = STAGE != kStageDeriv;   // the derivatives do not evaluate H
@@ -324,6 +337,9 @@ hipError_t launch_stage(const hjw_grid* g, StageArgs<T, P> a) {
     else if (g->dim == 2 && kNarrow && segment(g) == 4)
         hipLaunchKernelGGL((k_stage2d<T, P, STAGE, 16, kNarrow ? 4 : 8, false>), grid,
                            dim3(threads2d(16, 4)), 0, g->stream, a);
+    else if (g->dim == 2 && kDense && dense_tiles(g))
+        hipLaunchKernelGGL((k_stage2d<T, P, STAGE, 16, 8, false, kDense>), grid,
+                           dim3(threads2d(16, 8)), 0, g->stream, a);
     else if (g->dim == 2)
         hipLaunchKernelGGL((k_stage2d<T, P, STAGE, 16, 8, false>), grid, dim3(threads2d(16, 8)),
                            0, g->stream, a);

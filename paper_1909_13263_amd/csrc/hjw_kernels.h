@@ -326,9 +326,9 @@ __device__ inline bool stage_entry(const StageArgs<T, P>& a, int bid, double& dt
 // One workgroup's share of a stage on a 2-D grid: bid is the workgroup's index among
 // the grid's nbx * nby tiles; threads2d(TY, S) threads, half row and half column
 // threads, each marching S nodes.
-template <typename T, typename P, int STAGE, int TY, int S, bool TIMED>
+template <typename T, typename P, int STAGE, int TY, int S, bool TIMED, bool DENSE = false>
 __device__ inline void stage_tile2d(const StageArgs<T, P>& a, int bid) {
-    using TL = Tile<T, P, kTX, TY, S, S>;
+    using TL = Tile<T, P, kTX, TY, S, S, !DENSE>;
     static_assert(TL::kThreads == threads2d(TY, S), "launch bounds");
     constexpr bool kCenter = STAGE == kStageMid || STAGE == kStageLast;
     __shared__ P phiL[TL::kPhiElems];
@@ -390,11 +390,11 @@ __device__ inline void stage_tile2d(const StageArgs<T, P>& a, int bid) {
 }
 
 // TIMED: the grid's Hamiltonian may be the time- and phi-dependent family; the kernels of
-// every other family are compiled without its code.
-template <typename T, typename P, int STAGE, int TY, int S, bool TIMED>
-__global__ __launch_bounds__(threads2d(TY, S), fp64_waves(sizeof(T), TY)) void k_stage2d(
+// every other family are compiled without its code.  DENSE: FP64 with four tiles a CU.
+template <typename T, typename P, int STAGE, int TY, int S, bool TIMED, bool DENSE = false>
+__global__ __launch_bounds__(threads2d(TY, S), fp64_waves(sizeof(T), TY, DENSE)) void k_stage2d(
     StageArgs<T, P> a) {
-    stage_tile2d<T, P, STAGE, TY, S, TIMED>(a, int(blockIdx.x));
+    stage_tile2d<T, P, STAGE, TY, S, TIMED, DENSE>(a, int(blockIdx.x));
 }
 
 template <typename T, typename P, int STAGE, bool TIMED>

@@ -90,8 +90,12 @@ constexpr int kTX = 64;
 constexpr int kTX1 = 1024, kS1 = 4;
 // Threads of a 2-D workgroup: as many row threads as column threads.
 constexpr int threads2d(int ty, int seg) { return 2 * (kTX / seg) * ty; }
-// Waves per SIMD asked of the FP64 16-row stage kernels (3 tiles a CU; VGPRs <= 168).
-constexpr int fp64_waves(int elem, int ty) { return elem == 8 && ty == 16 ? 3 : 1; }
+// Waves per SIMD asked of the FP64 16-row stage kernels, which is also the tiles a CU holds:
+// three (VGPRs <= 168, none spilled), or four of the dense kernels (<= 128, 8-11 spilled, and
+// no copy of phi^n in LDS).
+constexpr int fp64_waves(int elem, int ty, bool dense) {
+    return elem == 8 && ty == 16 ? (dense ? 4 : 3) : 1;
+}
 
 // Step state kept on the device so that whole steps can be replayed from a graph.
 struct DevState {
@@ -782,7 +786,7 @@ __host__ __device__ inline P stage_value(const StageArgs<T, P>& a, int64_t i, in
 // 2 * kHalf threads: threads [0, kHalf) march the rows (phase X) while threads
 // [kHalf, 2 kHalf) march the columns (phase Y) at the same time; after a barrier the
 // column threads combine their phi_y^-+ with the phi_x^-+ left in LDS by the row threads.
-template <typename T, typename P, int TX, int TY, int SX, int SY>
+template <typename T, typename P, int TX, int TY, int SX, int SY, bool CENTER = true>
 struct Tile {
     static constexpr int kHalf = TY * (TX / SX);
     static constexpr int kThreads = 2 * kHalf;
@@ -791,7 +795,10 @@ struct Tile {
     static constexpr int UW = TX + 1;      // pitch of the phi_x results
     static constexpr int kPhiElems = PH * PW;
     static constexpr int kUElems = 2 * TY * UW;
-    static constexpr int kCenterElems = TX * TY;   // phi^n on the tile (second/third stage)
+    // phi^n on the tile (second/third stage); without CENTER the finish reads it from memory
+    // again.
+    static constexpr bool kCenterLds = CENTER;
+    static constexpr int kCenterElems = kCenterLds ? TX * TY : 1;
     static_assert(TX * (TY / SY) == kHalf, "phase Y covers the tile columns with as many threads");
     static_assert(kHalf % 64 == 0, "row and column threads are whole waves");
 
@@ -806,7 +813,7 @@ struct Tile {
                                          int64_t y0, double dt, double ax, double ay, P* phiL,
                                          P* pnL) {
         static_assert((TX & (TX - 1)) == 0 && (TY & (TY - 1)) == 0, "power-of-two tile");
-        constexpr bool kCenter = STAGE == kStageMid || STAGE == kStageLast;
+        constexpr bool kCenter = kCenterLds && (STAGE == kStageMid || STAGE == kStageLast);
         // element e of this thread's j-th load; the last round is partial, and its idle
         // threads load a valid element whose value they drop
         auto element = [&](int j) {
@@ -1004,7 +1011,7 @@ struct Tile {
                 const Flux3<T> f = g.f[j];
                 const double rr = double(f.h) - (mul_rn(ax, double(f.dx)) + mul_rn(ay, double(f.dy)));
                 phiL[r * PW + c] = P(fma(-dt, rr, double(g.pn[j])));
-                if (e < TY * TX) pnL[e] = g.pn[j];
+                if (kCenterLds && e < TY * TX) pnL[e] = g.pn[j];
             }
         }
     }
@@ -1097,13 +1104,17 @@ struct Tile {
         const T* u0 = uL + row0 * UW + col;
         const T* v0 = vL + seg * kKeep * TX + col;
         const P* s0 = phiL + (row0 + 3) * PW + col + 3;
-        const P* n0 = Fin::kUsesPn ? pnL + row0 * TX + col : pnL;
+        const P* n0 = Fin::kUsesPn && kCenterLds ? pnL + row0 * TX + col : pnL;
+        P pn[kKeep];
+#pragma unroll
+        for (int j = 0; j < kKeep; ++j)
+            pn[j] = !Fin::kUsesPn ? P(0) : kCenterLds ? n0[j * TX] : fin.phi_n(col, row0 + j);
 #pragma unroll
         for (int j = 0; j < kKeep; ++j) {
             const T m = first == 0 ? vm[j] : v0[j * TX];   // first is uniform: a scalar test
             const T p = first == 0 ? vp[j] : v0[kVElems / 2 + j * TX];
             fin.template node<MODE>(col, row0 + j, u0[j * UW], u0[TY * UW + j * UW], m, p,
-                                   s0[j * PW], Fin::kUsesPn ? n0[j * TX] : P(0));
+                                   s0[j * PW], pn[j]);
         }
     }
 };
@@ -1229,6 +1240,12 @@ struct Finisher {
     __host__ __device__ bool extended() const {
         return a.bcx == kBcDirichlet ||
                (dim == 2 && (a.bcy == kBcDirichlet || a.ham == kHCurvature));
+    }
+
+    // phi^n at a node of the tile (0 outside the grid).
+    __host__ __device__ P phi_n(int col, int row) const {
+        if (col >= room_x || row >= room_y) return P(0);
+        return at(a.phi_n + (int64_t(int(y0) + row) * a.nx + x0), uint32_t(col));
     }
 
     // The node variant of this launch, uniform over it: callers pick it once, outside
