@@ -518,7 +518,8 @@ __host__ __device__ inline void sweep(const P* line, int stride, P ihP, T ih, T 
 // ---------------------------------------------------------------- Hamiltonians
 // H(u, v) at the node (x, y); only the control Hamiltonian of Example 3.11 depends on
 // the position (the family that depends on t and phi, TIMED, is evaluated by the
-// finisher, which holds the stage time):
+// finisher, which holds the stage time).  Every product that feeds a sum, here or in the
+// caller, is rounded alone or in a written-out multiply-add, so that all kernels round alike:
 //   LINEAR a u + b v; BURGERS s^2/2; NEGCOS -cos s; QUARTIC (s^2-1)(s^2-4)/4 with
 //   s = a u + b v + c; NORM and CURVATURE k0 sqrt(u^2 + v^2 + k1) (the curvature term
 //   is added by the finisher);
@@ -530,22 +531,22 @@ __host__ __device__ inline T hamiltonian(int kind, const T* p, T u, T v, T x, T 
         return mul_rn(p[0], u) + mul_rn(p[1], v);
     case kHBurgers: {
         const T s = (mul_rn(p[0], u) + mul_rn(p[1], v)) + p[2];
-        return T(0.5) * s * s;
+        return mul_rn(T(0.5) * s, s);
     }
     case kHNegcos:
         return -cos_t((mul_rn(p[0], u) + mul_rn(p[1], v)) + p[2]);
     case kHQuartic: {
         const T s = (mul_rn(p[0], u) + mul_rn(p[1], v)) + p[2];
-        const T s2 = s * s;
-        return T(0.25) * ((s2 - T(1)) * (s2 - T(4)));
+        return mul_rn(T(0.25), mul_rn(fma_t(s, s, T(-1)), fma_t(s, s, T(-4))));
     }
     case kHControl: {
         const T sy = sin_t(y);
         const T sgn = T((v > T(0)) - (v < T(0)));
-        return sy * u + (sin_t(x) + sgn) * v - T(0.5) * sy * sy - (T(1) - cos_t(x));
+        const T uv = fma_t(u, sy, mul_rn(sin_t(x) + sgn, v));
+        return fma_t(sy, mul_rn(T(-0.5), sy), uv) - (T(1) - cos_t(x));
     }
     default:
-        return p[0] * sqrt_t((mul_rn(u, u) + mul_rn(v, v)) + p[1]);
+        return mul_rn(p[0], sqrt_t((mul_rn(u, u) + mul_rn(v, v)) + p[1]));
     }
 }
 
@@ -1301,8 +1302,8 @@ struct Finisher {
         const T ub = T(0.5) * (up + um), vb = T(0.5) * (vp + vm);
         const T Dx = T(0.5) * (up - um), Dy = T(0.5) * (vp - vm);
         // node coordinates, for the position-dependent Hamiltonian only
-        const T xn = a.ham == kHControl ? T(a.x0 + double(i) * a.dxD) : T(0);
-        const T yn = a.ham == kHControl ? T(a.y0 + double(j) * a.dyD) : T(0);
+        const T xn = a.ham == kHControl ? T(fma_t(double(i), a.dxD, a.x0)) : T(0);
+        const T yn = a.ham == kHControl ? T(fma_t(double(j), a.dyD, a.y0)) : T(0);
         T H;
         if (MODE == kNodeTimed && a.ham == kHTimed) {
             // ps is this stage's own value at the node

@@ -88,8 +88,10 @@ def test_resident_solve_is_the_stages_bits(shape, bc, prec):
     alpha and the derivative box, in two calls (the second continues), and once more from a
     new phi on the same grid (the mailboxes hold the first solve's words)."""
     kinds = [(O.H_BURGERS, (1.0, 1.0 if len(shape) == 2 else 0.0, 1.0)), (O.H_NORM, (1.0, 0.0)),
-             (O.H_NEGCOS, (1.0, 0.0, 0.3)), (O.H_TIMED, (0.8, -0.6 * (len(shape) - 1), 5.0, 0.9))]
-    ham, params = kinds[(sum(shape) + prec) % 4]
+             (O.H_NEGCOS, (1.0, 0.0, 0.3)), (O.H_TIMED, (0.8, -0.6 * (len(shape) - 1), 5.0, 0.9)),
+             (O.H_QUARTIC, (1.0, 0.0, 0.2)), (O.H_CONTROL, ()) if len(shape) == 2 else
+             (O.H_LINEAR, (0.7, 0.0))]
+    ham, params = kinds[(sum(shape) + prec) % 6]
     print(f"resident {shape} bc={bc} prec={prec} ham={ham}", flush=True)
     out = []
     for resident in (True, False):
