@@ -120,10 +120,10 @@ constexpr int kUnits = 256;
 // cells, as long as all fit: four of them a compute unit by LDS with the FP32 stencil, two in
 // FP64 (at three, of which some units then hold two, 768^2 took 57 us a step, launches per
 // stage 39).  us a step (Burgers, best of the launches per stage -> this launch):
-//   FP32 stencil  64^2 20.2 -> 13.2 (64 x 8: 14.6, 64 x 16: 17.6)   256^2 18.6 -> 12.8
-//                 320^2 18.3 -> 13.8 (64 x 4: 14.7)   512^2 19.0 -> 16.4 (64 x 8: 18.1)
-//                 640^2 23.8 -> 21.3   900^2 40.6 -> 35.5   1024^2 37.8 -> 30.4
-//   FP64          64^2 37.3 -> 18.7 (64 x 8: 23.2)   256^2 38.0 -> 19.3
+//   FP32 stencil  48^2 20.6 -> 12.1   128^2 19.7 -> 11.8   256^2 18.6 -> 13.1 (64 x 8: 13.6)
+//                 320^2 18.3 -> 13.9 (64 x 4: 14.7)   512^2 19.0 -> 16.1 (64 x 8: 18.1)
+//                 640^2 23.8 -> 20.9   900^2 40.6 -> 35.0   1024^2 37.8 -> 29.4
+//   FP64          48^2 37.7 -> 16.3   256^2 38.0 -> 18.2 (64 x 8: 23.9)   320^2 38.4 -> 24.4
 //                 400^2 36.0 -> 32.0   512^2 27.9 -> 21.6   640^2 32.2 -> 29.2
 int resident_tile(const hjw_grid* g, int* seg, Split* sx, Split* sy) {
     *seg = 1;
@@ -135,7 +135,7 @@ int resident_tile(const hjw_grid* g, int* seg, Split* sx, Split* sy) {
     }
     const int64_t bx = (g->nx + kTX - 1) / kTX;
     const struct { int ty, seg; int64_t most; } option[] = {
-        {4, 2, kUnits}, {8, 2, kUnits}, {16, 4, kUnits},
+        {4, 0, kUnits}, {8, 2, kUnits}, {16, 4, kUnits},
         {16, 8, g->prec == HJW_FP64 ? 2 * kUnits : 4 * kUnits}};
     for (const auto& o : option) {
         if (bx * ((g->ny + o.ty - 1) / o.ty) > o.most) continue;
@@ -479,7 +479,7 @@ const void* resident_kernel(const hjw_grid* g) {
                                 g->ham == HJW_H_TIMED || g->llf);
 }
 int resident_threads(const hjw_grid* g) {
-    return g->dim == 1 ? kResidentTX1 : threads2d(g->resident_ty, g->resident_seg);
+    return g->dim == 1 ? kResidentThreads1 : resident_threads2d(g->resident_ty, g->resident_seg);
 }
 
 // Whether the grid's steps can go through the resident launch: default options, a family

@@ -319,12 +319,12 @@ struct Words {
 template <typename T, typename P, int TX, int TY, int S>
 struct EmuResident {
     static constexpr bool k2D = TY > 1;
-    using TL2 = Tile<T, P, kTX, k2D ? TY : 16, k2D ? S : 8, k2D ? S : 8>;
-    using TL1 = Tile1D<T, P, kResidentTX1, 1>;
-    static constexpr int kThreads = k2D ? TL2::kThreads : TL1::kThreads;
+    using RT = ResidentTile<T, P, k2D ? TY : 16, k2D ? S : 8>;
+    using TL2 = typename RT::TL;
+    using TL1 = ResidentTile1D<T, P>;
+    static constexpr int kThreads = k2D ? RT::kThreads : kResidentThreads1;
     static constexpr int kPhi = k2D ? TL2::kPhiElems : TL1::kPhiElems;
     static constexpr int kU = k2D ? TL2::kUElems : TL1::kUElems;
-    using RT = ResidentTile<T, P, k2D ? TY : 16, k2D ? S : 8>;
     using BD = Border<T, P, TX, TY, k2D ? TL2::PW : TL1::PW, k2D ? 2 : 1, kThreads>;
 
     struct TileState {
@@ -363,10 +363,10 @@ struct EmuResident {
         ts.uL.assign(kU, T(NAN));
         if constexpr (k2D) {
             ts.vL.assign(RT::kVElems, T(NAN));
-            for (int t = 0; t < TL2::kHalf; ++t) TL2::sweep_x(t, a, ts.phiL.data(), ts.uL.data());
-            for (int t = 0; t < TL2::kHalf; ++t) RT::sweep_y(t, a, ts.phiL.data(), ts.vL.data());
+            for (int t = 0; t < kThreads; ++t)
+                RT::sweeps(t, a, ts.phiL.data(), ts.uL.data(), ts.vL.data());
         } else {
-            for (int t = 0; t < kThreads; ++t) TL1::sweep_x(t, a, ts.phiL.data(), ts.uL.data());
+            for (int t = 0; t < kThreads; ++t) TL1::sweep(t, a, ts.phiL.data(), ts.uL.data());
         }
     }
     static Flux3<T> flux_of(const TileState& ts, int c, int j) {
@@ -395,7 +395,7 @@ struct EmuResident {
             else nodes(std::integral_constant<int, kNodePlain>{});
         } else {
             for (int c = 0; c < ts.s.w; ++c) {
-                fin(c, 0, ts.uL[c], ts.uL[kResidentTX1 + c], T(0), T(0), ts.phiL[c + 3], ts.pn[c]);
+                fin(c, 0, ts.uL[c], ts.uL[TL1::kUElems / 2 + c], T(0), T(0), ts.phiL[c + 3], ts.pn[c]);
                 hand(c, 0, fin.sink);
             }
         }
@@ -517,7 +517,7 @@ int resident(const Problem& pr, double* phi, double t, double t_final, double cf
     int rc = -1;
     if (pr.dim == 1) rc = resident_run<T, P, kResidentTX1, 1, 1>(e, st, steps);
     else if (ty == 8 && seg == 2) rc = resident_run<T, P, kTX, 8, 2>(e, st, steps);
-    else if (ty == 4 && seg == 2) rc = resident_run<T, P, kTX, 4, 2>(e, st, steps);
+    else if (ty == 4 && seg == 0) rc = resident_run<T, P, kTX, 4, 0>(e, st, steps);
     else if (ty == 16 && seg == 4) rc = resident_run<T, P, kTX, 16, 4>(e, st, steps);
     else if (ty == 16 && seg == 8) rc = resident_run<T, P, kTX, 16, 8>(e, st, steps);
     for (size_t k = 0; k < e.n; ++k) phi[k] = double(e.phi.data()[k]);

@@ -21,15 +21,15 @@
 // than kJoinTicks closes it, whereupon every workgroup (also one that starts later) leaves
 // without having changed anything and the host steps with the launches per stage.  Once all
 // have arrived every later wait ends; the waits are bounded all the same.
-// What bounds it.  On small grids a step is a chain of latencies: 256^2 (256 tiles of 64 x 4,
-// FP32 stencil) 14.2 us a step = sweeps 2.9, finishes and phi_1 3.0, the box's two hops and the
-// plan 4.3, two border exchanges 3.0 and barriers; a hop between two workgroups, store to
-// load, takes about 1.5 us.  At 1024^2 (four 64 x 16 tiles a compute unit) it is the issue of
+// What bounds it.  On small grids a step is a chain of latencies: with a march of two nodes a
+// thread, 256^2 (256 tiles of 64 x 4, FP32 stencil) took 14.2 us a step = sweeps 2.9, finishes
+// and phi_1 3.0, the box's two hops and the plan 4.3, two border exchanges 3.0 and barriers; a
+// hop between two workgroups, store to load, takes about 1.5 us, the plan's FP64 chain 0.7.  At 1024^2 (four 64 x 16 tiles a compute unit) it is the issue of
 // vector instructions: a wave instruction takes 4 cycles of its SIMD here (the counters give
 // 1.04 quad-cycles each), so the 1200 instructions of a wave and stage make 24 of the 30 us a
 // step; the launches per stage take 38.  Whole solves, launches per stage -> this launch:
-// Burgers 1024^2 8.5 -> 6.9 ms (FP32 stencil), 1-D N = 160 0.92 -> 0.31 ms, Dirichlet 80^2 FP64
-// 7.9 -> 3.1 ms, level set 512^2 FP64 8.7 -> 7.2 ms.
+// Burgers 1024^2 8.1 -> 6.5 ms (FP32 stencil), 1-D N = 160 0.92 -> 0.26 ms, Dirichlet 80^2 FP64
+// 7.9 -> 2.9 ms, level set 512^2 FP64 8.7 -> 7.0 ms.
 // Nodes' results and phi^n stay in LDS, not in registers, from sweep to finish: with them in
 // registers the unrolled finishes of three stages and all families were 118 KB of code with
 // scratch traffic, and a 1024^2 step took 50 us.  Borders are sent from LDS in the mailboxes'
@@ -52,6 +52,7 @@ inline Split split_axis(int64_t n, int most) {
     return Split{nb, int(n / nb), int(n % nb)};
 }
 
+constexpr int kResidentTX1 = 255, kResidentThreads1 = 256;   // 1-D: nodes and threads of a tile
 constexpr int kGroup = 64;          // workgroups whose ranges one leader reduces
 constexpr int kMaxResident = 1024;  // workgroups of a launch (16 groups)
 enum { kWest = 0, kEast, kSouth, kNorth };
@@ -356,27 +357,67 @@ struct Border {
 // The sweeps of a resident 2-D tile: as the stage kernels', but the columns' results go to LDS
 // too, so that every node's four derivatives lie there, and a finish may take its nodes in any
 // order, in a loop, with nothing of theirs in registers from stage to stage.
+// S = 0: a thread per cell instead of a thread per segment (65 cells a row, TY + 1 a column):
+// the march is one cell long.  On tiles of four rows that takes 640 threads, and no cell is
+// computed twice.  Against two nodes a thread (three cells, 256 threads): 48^2 13.6 -> 12.1 us a
+// step (FP64 17.7 -> 16.3), 128^2 12.8 -> 11.8, Dirichlet 80^2 FP64 19.3 -> 17.8; in 1-D, where a
+// thread marched one node (two cells), N = 160 8.0 -> 6.0, N = 5000 11.2 -> 9.3.
+constexpr int cell_waves_x(int ty) { return (ty * (kTX + 1) + 63) / 64; }
+constexpr int resident_threads2d(int ty, int seg) {
+    return seg == 0 ? 64 * (cell_waves_x(ty) + ty + 1) : threads2d(ty, seg);
+}
 template <typename T, typename P, int TY, int S>
 struct ResidentTile {
-    using TL = Tile<T, P, kTX, TY, S, S>;
-    static constexpr int kThreads = TL::kThreads;
+    using TL = Tile<T, P, kTX, TY, S ? S : 2, S ? S : 2>;
+    static constexpr int kThreads = resident_threads2d(TY, S);
     static constexpr int kNodes = kTX * TY;
     static constexpr int kVElems = 2 * kNodes;
-    static_assert(kNodes % kThreads == 0, "every thread finishes as many nodes");
+    static_assert(kThreads <= 1024 && kNodes % 64 == 0, "one workgroup, rows are waves");
 
-    __host__ __device__ static void sweep_y(int t, const StageArgs<T, P>& a, const P* phiL, T* vL) {
-        const int col = t % kTX, seg = t / kTX;
-        struct ToLds {
-            T* base;
-            __host__ __device__ void minus(int k, T v) const { base[k * kTX] = v; }
-            __host__ __device__ void plus(int k, T v) const { base[kNodes + k * kTX] = v; }
-        };
-        const ToLds out{vL + seg * S * kTX + col};
-        const P* line = phiL + seg * S * TL::PW + col + 3;
+    template <int SEG, class Out>
+    __host__ __device__ static void march(const P* line, int stride, const StageArgs<T, P>& a, P ih,
+                                          T ihT, T eps, const Out& out) {
         if (a.scheme == kSchemeJP)
-            sweep_emit<T, P, S, kSchemeJP>(line, TL::PW, a.ihy, a.ihyT, a.epsy, out);
+            sweep_emit<T, P, SEG, kSchemeJP>(line, stride, ih, ihT, eps, out);
         else
-            sweep_emit<T, P, S, kSchemeL>(line, TL::PW, a.ihy, a.ihyT, a.epsy, out);
+            sweep_emit<T, P, SEG, kSchemeL>(line, stride, ih, ihT, eps, out);
+    }
+    // Both sweeps, thread id's share.
+    __host__ __device__ static void sweeps(int id, const StageArgs<T, P>& a, const P* phiL, T* uL,
+                                           T* vL) {
+        if constexpr (S == 0) {
+            constexpr int kX = 64 * cell_waves_x(TY);
+            // the cell's left side is the node before it, its right side the node at it
+            struct Cell {
+                T *m, *p;
+                bool right, left;
+                __host__ __device__ void minus(int, T v) const { if (right) *m = v; }
+                __host__ __device__ void plus(int, T v) const { if (left) *p = v; }
+            };
+            if (id < kX) {
+                const int q = id < TY * (kTX + 1) ? id : 0;   // idle threads repeat the first cell
+                const int row = q / (kTX + 1), c = q % (kTX + 1);
+                T* u = uL + row * TL::UW + c;
+                march<0>(phiL + (row + 3) * TL::PW + c, 1, a, a.ihx, a.ihxT, a.epsx,
+                         Cell{u, u + TY * TL::UW - 1, id == q && c < kTX, id == q && c > 0});
+            } else {
+                const int q = id - kX, it = q / kTX, col = q % kTX;
+                T* v = vL + it * kTX + col;
+                march<0>(phiL + it * TL::PW + col + 3, TL::PW, a, a.ihy, a.ihyT, a.epsy,
+                         Cell{v, v + kNodes - kTX, it < TY, it > 0});
+            }
+        } else if (id < TL::kHalf) {
+            TL::sweep_x(id, a, phiL, uL);
+        } else {
+            const int t = id - TL::kHalf, col = t % kTX, seg = t / kTX;
+            struct ToLds {
+                T* base;
+                __host__ __device__ void minus(int k, T v) const { base[k * kTX] = v; }
+                __host__ __device__ void plus(int k, T v) const { base[kNodes + k * kTX] = v; }
+            };
+            march<S>(phiL + seg * S * TL::PW + col + 3, TL::PW, a, a.ihy, a.ihyT, a.epsy,
+                     ToLds{vL + seg * S * kTX + col});
+        }
     }
     // The node's places in uL and vL; once its derivatives have been read, its flux record
     // takes three of the four.
@@ -396,6 +437,27 @@ struct ResidentTile {
                                          P pn) {
         fin.template node<MODE>(c, r, uL[u_at(c, r)], uL[TY * TL::UW + u_at(c, r)], vL[v_at(c, r)],
                                 vL[kNodes + v_at(c, r)], ps, pn);
+    }
+};
+
+// A 1-D tile: a thread a cell (one more than nodes), then a thread a node.
+template <typename T, typename P>
+struct ResidentTile1D {
+    static constexpr int PW = kResidentTX1 + 7;   // 255 nodes and their halos, and one spare
+    static constexpr int kPhiElems = PW;
+    static constexpr int kUElems = 2 * kResidentThreads1;
+    __host__ __device__ static void sweep(int t, const StageArgs<T, P>& a, const P* phiL, T* uL) {
+        struct Cell {
+            T* u;
+            bool left;
+            __host__ __device__ void minus(int, T v) const { u[0] = v; }
+            __host__ __device__ void plus(int, T v) const { if (left) u[kUElems / 2 - 1] = v; }
+        };
+        const Cell out{uL + t, t > 0};
+        if (a.scheme == kSchemeJP)
+            sweep_emit<T, P, 0, kSchemeJP>(phiL + t, 1, a.ihx, a.ihxT, a.epsx, out);
+        else
+            sweep_emit<T, P, 0, kSchemeL>(phiL + t, 1, a.ihx, a.ihxT, a.epsx, out);
     }
 };
 
@@ -655,15 +717,17 @@ __device__ inline int fresh(int x) {
 }
 
 // Waves per SIMD asked of the resident kernels.
-constexpr int resident_waves(int elem, int ty) { return elem == 8 ? (ty == 16 ? 3 : 4) : 4; }
+constexpr int resident_waves(int elem, int ty, int seg) {
+    return seg == 0 ? 3 : elem == 8 && ty == 16 ? 3 : 4;
+}
 
 template <typename T, typename P, int TY, int S, bool TIMED>
-__global__ __launch_bounds__(threads2d(TY, S), resident_waves(sizeof(T), TY)) void k_resident2d(
+__global__ __launch_bounds__(resident_threads2d(TY, S), resident_waves(sizeof(T), TY, S)) void k_resident2d(
     StageArgs<T, P> a, ResidentArgs r) {
-    using TL = Tile<T, P, kTX, TY, S, S>;
     using RT = ResidentTile<T, P, TY, S>;
-    using BD = Border<T, P, kTX, TY, TL::PW, 2, TL::kThreads>;
-    constexpr int NW = TL::kThreads / 64;
+    using TL = typename RT::TL;
+    using BD = Border<T, P, kTX, TY, TL::PW, 2, RT::kThreads>;
+    constexpr int NW = RT::kThreads / 64;
     __shared__ P phiL[TL::kPhiElems];
     __shared__ P pnL[RT::kNodes];   // phi^n of the tile's nodes
     __shared__ T uL[TL::kUElems];
@@ -671,7 +735,7 @@ __global__ __launch_bounds__(threads2d(TY, S), resident_waves(sizeof(T), TY)) vo
     __shared__ ResidentShared<NW> sh;
     __shared__ DevState sh_tn;   // t_n of the step, for the time-dependent family
     const int tid = threadIdx.x;
-    __builtin_assume(tid >= 0 && tid < TL::kThreads);
+    __builtin_assume(tid >= 0 && tid < RT::kThreads);
     const Spot s = make_spot(r, tile_of_block(int(blockIdx.x), r.count, r.remap), 2, a.bcx, a.bcy);
     if (tid == 0) {
         sh.go = resident_join(r);
@@ -699,9 +763,9 @@ __global__ __launch_bounds__(threads2d(TY, S), resident_waves(sizeof(T), TY)) vo
         if (c >= s.w) return;
         int row = uniform_int(id / kTX);
 #pragma unroll 1
-        for (; row < s.h; row += TL::kThreads / kTX) f(c, row);
+        for (; row < s.h; row += RT::kThreads / kTX) f(c, row);
     };
-    for (int e = tid; e < RT::kNodes; e += TL::kThreads)
+    for (int e = tid; e < RT::kNodes; e += RT::kThreads)
         pnL[e] = phiL[BD::own(e % kTX, e / kTX)];
     double dt = 0.0, ax = 0.0, ay = 0.0;
     bool bad = false;       // a non-finite phi^{n+1} of the last step taken, here
@@ -733,11 +797,11 @@ __global__ __launch_bounds__(threads2d(TY, S), resident_waves(sizeof(T), TY)) vo
     // the border of phi_2 or phi^{n+1} to the neighbours, and theirs
     auto exchange = [&](u64* mail, unsigned int tag) {
         __syncthreads();
-        BD::send_phi(fresh(tid), TL::kThreads, s, phiL, tag, mail);
+        BD::send_phi(fresh(tid), RT::kThreads, s, phiL, tag, mail);
         typename BD::template Received<Tagged<P>, BD::kRounds> got;
         const int id = fresh(tid);
-        BD::expect(id, TL::kThreads, s, got);
-        if (!wait_for(r, [&] { return BD::look(id, TL::kThreads, s, tag, mail, got); }))
+        BD::expect(id, RT::kThreads, s, got);
+        if (!wait_for(r, [&] { return BD::look(id, RT::kThreads, s, tag, mail, got); }))
             sh.fail = 1;
 #pragma unroll
         for (int k = 0; k < BD::kRounds; ++k)
@@ -755,11 +819,8 @@ __global__ __launch_bounds__(threads2d(TY, S), resident_waves(sizeof(T), TY)) vo
     for (;;) {
         const unsigned int tag = r.epoch + unsigned(step);
         const int id = fresh(tid);
-        __builtin_assume(id >= 0 && id < TL::kThreads);
-        if (id < TL::kHalf)
-            TL::sweep_x(id, a, phiL, uL);
-        else
-            RT::sweep_y(id - TL::kHalf, a, phiL, vL);
+        __builtin_assume(id >= 0 && id < RT::kThreads);
+        RT::sweeps(id, a, phiL, uL, vL);
         if (TIMED && stage == 0 && tid == 0) sh_tn.t = sh.st.t;
         __syncthreads();
         if (stage == 0) {
@@ -770,7 +831,7 @@ __global__ __launch_bounds__(threads2d(TY, S), resident_waves(sizeof(T), TY)) vo
             resident_fold(sh, fin.lo_u, fin.hi_u, fin.lo_v, fin.hi_v, fin.bad || bad);
             __syncthreads();
             // the first wave reduces the box and plans while the others exchange the records
-            constexpr int kOthers = TL::kThreads - 64;
+            constexpr int kOthers = RT::kThreads - 64;
             constexpr int kFluxRounds = (BD::kElems + kOthers - 1) / kOthers;
             typename BD::template Received<TaggedFlux<T>, kFluxRounds> got;
             if (tid < 64) {
@@ -836,20 +897,18 @@ __global__ __launch_bounds__(threads2d(TY, S), resident_waves(sizeof(T), TY)) vo
     resident_close(a, r, s.tile, sh.st, sh.fail, bad);
 }
 
-// 1-D: one node a thread.
-constexpr int kResidentTX1 = 256;
 template <typename T, typename P, bool TIMED>
-__global__ __launch_bounds__(kResidentTX1) void k_resident1d(StageArgs<T, P> a, ResidentArgs r) {
-    using TL = Tile1D<T, P, kResidentTX1, 1>;
-    using BD = Border<T, P, kResidentTX1, 1, TL::PW, 1, kResidentTX1>;
-    constexpr int NW = kResidentTX1 / 64;
-    __shared__ P phiL[TL::kPhiElems];
-    __shared__ T uL[TL::kUElems];
+__global__ __launch_bounds__(kResidentThreads1) void k_resident1d(StageArgs<T, P> a, ResidentArgs r) {
+    using RT = ResidentTile1D<T, P>;
+    using BD = Border<T, P, kResidentTX1, 1, RT::PW, 1, kResidentThreads1>;
+    constexpr int NW = kResidentThreads1 / 64;
+    __shared__ P phiL[RT::kPhiElems];
+    __shared__ T uL[RT::kUElems];
     __shared__ Flux3<T> fluxL[kResidentTX1];
     __shared__ ResidentShared<NW> sh;
     __shared__ DevState sh_tn;
     const int tid = threadIdx.x;
-    __builtin_assume(tid >= 0 && tid < kResidentTX1);
+    __builtin_assume(tid >= 0 && tid < kResidentThreads1);
     const Spot s = make_spot(r, int(blockIdx.x), 1, a.bcx, a.bcy);
     if (tid == 0) {
         sh.go = resident_join(r);
@@ -857,7 +916,7 @@ __global__ __launch_bounds__(kResidentTX1) void k_resident1d(StageArgs<T, P> a, 
         sh.fail = 0;
         sh.active = 0;
     }
-    BD::template load<TL::kPhiElems>(tid, s, a, phiL);
+    BD::template load<RT::kPhiElems>(tid, s, a, phiL);
     __syncthreads();
     if (sh.go != 1) return;
     if (!(step_open(sh.st) && r.max_steps > 0)) {
@@ -878,7 +937,7 @@ __global__ __launch_bounds__(kResidentTX1) void k_resident1d(StageArgs<T, P> a, 
         fin.room_x = s.w;
         fin.room_y = 1;
         if (!mine) return;
-        const T um = uL[tid], up = uL[kResidentTX1 + tid];
+        const T um = uL[tid], up = uL[RT::kUElems / 2 + tid];
         const int mode = fin.mode();
         if (TIMED && mode == kNodeTimed)
             fin.template node<TIMED ? kNodeTimed : kNodePlain>(tid, 0, um, up, T(0), T(0),
@@ -892,9 +951,9 @@ __global__ __launch_bounds__(kResidentTX1) void k_resident1d(StageArgs<T, P> a, 
         typename BD::template Received<Tagged<P>, 1> got;
         __syncthreads();
         if (tid < 64) {
-            BD::send_phi(tid, kResidentTX1, s, phiL, tag, mail);
-            BD::expect(tid, kResidentTX1, s, got);
-            if (!wait_for(r, [&] { return BD::look(tid, kResidentTX1, s, tag, mail, got); }))
+            BD::send_phi(tid, kResidentThreads1, s, phiL, tag, mail);
+            BD::expect(tid, kResidentThreads1, s, got);
+            if (!wait_for(r, [&] { return BD::look(tid, kResidentThreads1, s, tag, mail, got); }))
                 sh.fail = 1;
             if (got.at[0] >= 0) phiL[got.at[0]] = got.rec[0].value();
         }
@@ -909,7 +968,7 @@ __global__ __launch_bounds__(kResidentTX1) void k_resident1d(StageArgs<T, P> a, 
 #pragma unroll 1
     for (;;) {
         const unsigned int tag = r.epoch + unsigned(step);
-        TL::sweep_x(tid, a, phiL, uL);
+        RT::sweep(tid, a, phiL, uL);
         if (TIMED && stage == 0 && tid == 0) sh_tn.t = sh.st.t;
         __syncthreads();
         if (stage == 0) {
@@ -922,11 +981,11 @@ __global__ __launch_bounds__(kResidentTX1) void k_resident1d(StageArgs<T, P> a, 
             if (tid < 64) {
                 resident_plan(a, r, s.tile, step, sh);
             } else if (tid < 128) {
-                BD::send_flux(tid - 64, kResidentTX1, s, [&](int c, int) { return fluxL[c]; }, tag,
+                BD::send_flux(tid - 64, kResidentThreads1, s, [&](int c, int) { return fluxL[c]; }, tag,
                               r.flux_mail);
-                BD::expect(tid - 64, kResidentTX1, s, got);
+                BD::expect(tid - 64, kResidentThreads1, s, got);
                 if (!wait_for(r, [&] {
-                        return BD::look(tid - 64, kResidentTX1, s, tag, r.flux_mail, got);
+                        return BD::look(tid - 64, kResidentThreads1, s, tag, r.flux_mail, got);
                     }))
                     sh.fail = 1;
             }

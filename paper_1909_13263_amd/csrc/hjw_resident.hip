@@ -14,7 +14,7 @@ namespace {
 template <typename T, typename P, bool OWN>
 const void* pick(int dim, int ty, int seg) {
     if (dim == 1) return reinterpret_cast<const void*>(k_resident1d<T, P, OWN>);
-    if (ty == 4 && seg == 2) return reinterpret_cast<const void*>(k_resident2d<T, P, 4, 2, OWN>);
+    if (ty == 4 && seg == 0) return reinterpret_cast<const void*>(k_resident2d<T, P, 4, 0, OWN>);
     if (ty == 8 && seg == 2) return reinterpret_cast<const void*>(k_resident2d<T, P, 8, 2, OWN>);
     if (ty == 16 && seg == 4) return reinterpret_cast<const void*>(k_resident2d<T, P, 16, 4, OWN>);
     if (ty == 16 && seg == 8) return reinterpret_cast<const void*>(k_resident2d<T, P, 16, 8, OWN>);

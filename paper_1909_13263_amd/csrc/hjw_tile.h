@@ -447,6 +447,7 @@ __host__ __device__ inline void weight_products(float MA2, float MB2, float MC2,
 //   q1 = c + (e2 + 2 e3)/6 for phi^- at x_i, and mirrored for phi^+ at x_{i-1}:
 //   qp1 = c - (e3 + 2 e2)/6, qp0 - qp1 = -D3b/3, qp2 - qp1 = -D3a/6.
 // So phi^- = q1 + (w0 (q0-q1) + w2 (q2-q1)) / (w0 + w1 + w2), and likewise phi^+.
+// S = 0: one cell, for both its sides: phi^-(p0) as minus(0, .) and phi^+(p0-1) as plus(-1, .).
 template <typename T, typename P, int S, int SCHEME, class Emit>
 __host__ __device__ inline void sweep_emit(const P* line, int stride, P ihP, T ih, T eps4,
                                            Emit&& emit) {
@@ -484,13 +485,13 @@ __host__ __device__ inline void sweep_emit(const P* line, int stride, P ihP, T i
         // multiple that takes the fewest instructions; powers of two round alike)
         const T xa = mul_rn(pBC, D3a), xb = mul_rn(pAB, D3b);
         const T p18AC = mul_rn(T(18), pAC);
-        if (it < S) {  // phi^- at node i: weights (1/10, 6/10, 3/10) on (A, B, C)
+        if (it < S || S == 0) {  // phi^- at node i: weights (1/10, 6/10, 3/10) on (A, B, C)
             const T q1 = fma_t(fma_t(T(2), e3, e2), T(1.0 / 6.0), c);
             const T num = fma_t(T(1.5), xb, xa);                // 3 (pBC D3a/3 + pAB D3b/2)
             const T den = fma_t(T(9), pAB, fma_t(T(3), pBC, p18AC));
             emit.minus(it, add_quot(q1, num, den));
         }
-        if (it > 0) {  // phi^+ at node i-1: the mirrored sub-stencils, (1/10, 6/10, 3/10) on (C, B, A)
+        if (it > 0 || S == 0) {  // phi^+ at node i-1: the mirrored sub-stencils, (1/10, 6/10, 3/10) on (C, B, A)
             const T qp1 = fma_t(-fma_t(T(2), e2, e3), T(1.0 / 6.0), c);
             const T num = fma_t(T(1.5), xa, xb);                // 3 (pAB D3b/3 + pBC D3a/2)
             const T den = fma_t(T(9), pBC, fma_t(T(3), pAB, p18AC));

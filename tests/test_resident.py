@@ -8,7 +8,7 @@ import emulator as EM
 import oracle as O
 from paper_1909_13263_amd import workloads as W
 
-TILES = [(4, 2), (8, 2), (16, 4), (16, 8)]
+TILES = [(4, 0), (8, 2), (16, 4), (16, 8)]
 # one tile; one past a tile's side; narrow last tiles; tiles of three rows or more only
 SHAPES = [(8, 8), (9, 65), (16, 64), (17, 129), (70, 150), (41, 200)]
 FAMILIES = [(O.H_LINEAR, (0.7, -0.4), 0), (O.H_BURGERS, (1.0, 1.0, 1.0), 0),
@@ -51,7 +51,7 @@ def test_emulated_resident_steps_are_the_stages_bits(tile, shape, family):
     assert np.array_equal(got, ref)
 
 
-@pytest.mark.parametrize("n", [8, 255, 256, 257, 700, 1030])
+@pytest.mark.parametrize("n", [8, 254, 255, 256, 257, 511, 700, 1030])
 @pytest.mark.parametrize("bc", [0, 1, 2])
 @pytest.mark.parametrize("prec", [0, 1, 2])
 def test_emulated_resident_steps_1d(n, bc, prec):
