@@ -33,6 +33,24 @@
 
 namespace hjw {
 
+// The solve that holds tile b, or -1 past the last tile.  Every lane looks at one of 64 starts,
+// so the answer is two memory round trips away (the starts are loaded beside their count) where
+// a binary search takes one per halving, all before the tile's own loads can be issued.
+// Measured (32 mixed requests served to the end, 568 steps, FP32 stencil): 27.4 -> 27.0 ms.
+// The starts lie in whole lines of 64; what lies past the count is loaded but not looked at.
+__device__ inline int solve_of_tile(const int* tile_start, const int* ngrids, int b) {
+    const int lane = int(threadIdx.x) & 63;
+    int first = tile_start[lane];
+    const int ng = *ngrids;
+    if (ng <= 0) return -1;
+    for (int j = 0;; j += 64) {
+        const int below = __popcll(__ballot(j + lane <= ng && first <= b));
+        if (j + below > ng) return -1;              // all of them, the end of the last included
+        if (below < 64) return j + below - 1;
+        first = tile_start[j + 64 + lane];          // (j + 64 <= ng here)
+    }
+}
+
 // One batched launch of a stage over all admitted solves.  table[g] holds solve g's
 // arguments with the parity it has when flip is 0; tile_start[g] is its first tile
 // (tile_start[ngrids] = total tiles).  Workgroups past the last tile exit.  The launch
@@ -44,17 +62,9 @@ __global__ __launch_bounds__(threads2d(16, S), fp64_waves(sizeof(T), 16, false))
                                                                    const int* tile_start,
                                                                    const int* ngrids, int flip,
                                                                    int plan_ready) {
-    const int ng = *ngrids;
     const int b = int(blockIdx.x % 8u * (gridDim.x / 8u) + blockIdx.x / 8u);
-    if (ng <= 0 || b >= tile_start[ng]) return;
-    int lo = 0, hi = ng;  // tile_start[lo] <= b < tile_start[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (tile_start[mid] <= b)
-            lo = mid;
-        else
-            hi = mid;
-    }
+    const int lo = solve_of_tile(tile_start, ngrids, b);
+    if (lo < 0) return;
     StageArgs<T, P> a = table[lo];
     a.par ^= flip;
     a.plan_ready = plan_ready;
@@ -774,6 +784,7 @@ hjw_status hjw_server_create(int prec, void* pool, size_t pool_bytes, int max_ac
     s->d_table = s->base + o;
     o += align256(size_t(max_active) * entry_bytes(prec));
     s->d_tile_start = reinterpret_cast<int*>(s->base + o);
+    // (whole lines of 64: solve_of_tile loads the last one entire)
     o += align256(size_t(max_active + 1) * sizeof(int));
     s->d_ngrids = reinterpret_cast<int*>(s->base + o);
     o += align256(sizeof(int));
