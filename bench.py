@@ -7,8 +7,10 @@ fused stages) runs on the GPU, from phi0 already resident in HBM.
 
 value = cells x RK stages / wall time for the FP32-stencil path (FP64 phi, FP64 time step
 and accumulation); the FP64 path is timed the same way and reported beside it.  The
-roofline object describes the dominant kernel, timed with HIP events on the library's
-stream right after the timed region, against the vector ALU peak (the bound of this path);
+roofline object describes the dominant kernel of the launches per stage (which larger grids
+run; a 1024 x 1024 grid itself steps in one launch with its tiles in LDS), timed with HIP
+events on the library's stream right after the timed region, against the vector ALU peak
+(the bound of this path);
 counter-derived traffic and instruction mixes ride along while the kernel sources match the
 ones they were measured on.  cpu_baseline is the
 FP64 oracle on the host cores, on a bounded sample of the same workload.
@@ -30,18 +32,19 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0                     # MI355X HBM3E, 8 TB/s
 # Vector ALU issue on gfx950, measured with a throughput probe (issue cycles of one wave64
-# instruction on a SIMD): FP32 add/mul/FMA and 32-bit integer operations 2 cycles (32 lanes
-# a cycle), FP64 operations and FP64 conversions 4 (16 lanes), FP32 transcendentals
-# (reciprocal, square root, logarithm) 8.  One lane-slot is one FP32 lane-operation, so the
-# FP32 peak is 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz = 78,643 G lane-slots/s (the published
-# 157.3 TFLOP/s FP32 vector peak counts an FMA as two flops); the FP64 peak in FP64
-# lane-operations is half of it (the published 78.6 TFLOP/s FP64 vector peak).
+# instruction on a SIMD): FP32 add/mul/FMA, FP64 operations and conversions 4, FP32
+# transcendentals (reciprocal, square root, logarithm) 8, FP64 seeds 16; the counters give
+# 1.04 quad-cycles per vector instruction.  One lane-slot is one FP32 lane-operation.  The
+# peak is the published one, 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz = 78,643 G lane-slots/s
+# (157.3 TFLOP/s, an FMA counted as two flops), which takes packed FP32; this library is
+# built without it, and can reach half.  The FP64 peak in FP64 lane-operations is half of it
+# too (the published 78.6 TFLOP/s FP64 vector peak).
 CYCLE_HZ = 2.4e9
 SIMDS = 256 * 4
 FP32_PEAK_GSLOTS = SIMDS * 32 * CYCLE_HZ / 1e9
 FP64_PEAK_GOPS = SIMDS * 16 * CYCLE_HZ / 1e9
-ISSUE_CYCLES = {"f32": 2, "i32": 2, "f64": 4, "cvt": 4, "i64": 4, "trans_f32": 8, "trans_f64": 16,
-                "other": 2}
+ISSUE_CYCLES = {"f32": 4, "i32": 4, "f64": 4, "cvt": 4, "i64": 4, "trans_f32": 8, "trans_f64": 16,
+                "other": 4}
 # Algorithmic work of one node-stage in 2-D (the operations of Section 2, Steps 2-5, per
 # node, both axes): about 200 add/mul/FMA plus 28 square roots, logarithms, divisions and
 # reciprocals (per axis 3 square roots and 3 logarithms for the arc-length antiderivatives,
@@ -67,47 +70,47 @@ def kernel_bytes_per_cell(phi_b, flux_b):
 # (SQ_INSTS_VALU_* x 64 / nodes).  Valid only while the kernel sources hash to the recorded
 # SHA-256; after any change the counter-derived fields are null until re-measured.
 MEASURED = {
-    "source_sha256": "cfc9faa4c751c743d53d3b32d2b35723fe6daf266cad6743c697fcb608e3db64",
+    "source_sha256": "cc4418190ba68c080c2bf3bb11c4e9db6ad164036a2f77f2946d315086682c8f",
     "runs": {
         "fp32_stencil/1024": {
-            "pre": {"fetch_kib": 4562.1, "write_kib": 12416.0, "traffic_bytes": 22057064,
-                    "valu_per_node": {"f32": 178.0, "f64": 6.5, "i32": 21.71, "cvt": 4.75, "i64": 2.36, "trans_f32": 13.25, "trans_f64": 0.0, "other": 38.81}},
-            "mid": {"fetch_kib": 11013.0, "write_kib": 8192.1, "traffic_bytes": 30943436,
-                    "valu_per_node": {"f32": 182.0, "f64": 17.88, "i32": 16.88, "cvt": 10.25, "i64": 3.86, "trans_f32": 13.25, "trans_f64": 0.06, "other": 33.53}},
-            "last": {"fetch_kib": 8636.0, "write_kib": 8194.2, "traffic_bytes": 26077440,
-                    "valu_per_node": {"f32": 182.0, "f64": 9.5, "i32": 14.34, "cvt": 5.25, "i64": 2.39, "trans_f32": 13.25, "trans_f64": 0.0, "other": 30.55}},
+            "pre": {"fetch_kib": 4556.3, "write_kib": 12416.0, "traffic_bytes": 22045284,
+                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 21.46, "cvt": 4.75, "i64": 2.36, "trans_f32": 13.25, "trans_f64": 0.0, "other": 40.81}},
+            "mid": {"fetch_kib": 11043.5, "write_kib": 8192.1, "traffic_bytes": 31005824,
+                    "valu_per_node": {"f32": 176.0, "f64": 17.88, "i32": 16.88, "cvt": 10.25, "i64": 3.86, "trans_f32": 13.25, "trans_f64": 0.06, "other": 35.28}},
+            "last": {"fetch_kib": 8637.0, "write_kib": 8194.2, "traffic_bytes": 26079488,
+                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 14.34, "cvt": 5.25, "i64": 2.39, "trans_f32": 13.25, "trans_f64": 0.0, "other": 32.3}},
         },
         "fp32_stencil/2048": {
-            "pre": {"fetch_kib": 17072.0, "write_kib": 49664.0, "traffic_bytes": 85819359,
-                    "valu_per_node": {"f32": 178.0, "f64": 6.5, "i32": 21.39, "cvt": 4.75, "i64": 2.06, "trans_f32": 13.25, "trans_f64": 0.0, "other": 38.38}},
-            "mid": {"fetch_kib": 42201.0, "write_kib": 32768.0, "traffic_bytes": 119982123,
-                    "valu_per_node": {"f32": 182.0, "f64": 16.0, "i32": 14.25, "cvt": 9.75, "i64": 2.91, "trans_f32": 13.25, "trans_f64": 0.0, "other": 28.02}},
-            "last": {"fetch_kib": 33424.3, "write_kib": 32770.2, "traffic_bytes": 102009614,
-                    "valu_per_node": {"f32": 182.0, "f64": 9.5, "i32": 13.92, "cvt": 5.25, "i64": 1.83, "trans_f32": 13.25, "trans_f64": 0.0, "other": 29.91}},
+            "pre": {"fetch_kib": 17060.3, "write_kib": 49664.0, "traffic_bytes": 85795403,
+                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 21.14, "cvt": 4.75, "i64": 2.06, "trans_f32": 13.25, "trans_f64": 0.0, "other": 40.38}},
+            "mid": {"fetch_kib": 42238.0, "write_kib": 32768.0, "traffic_bytes": 120057832,
+                    "valu_per_node": {"f32": 176.0, "f64": 16.0, "i32": 14.25, "cvt": 9.75, "i64": 2.91, "trans_f32": 13.25, "trans_f64": 0.0, "other": 29.77}},
+            "last": {"fetch_kib": 33423.5, "write_kib": 32770.2, "traffic_bytes": 102008101,
+                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 13.92, "cvt": 5.25, "i64": 1.83, "trans_f32": 13.25, "trans_f64": 0.0, "other": 31.66}},
         },
         "fp32_stencil/4096": {
-            "pre": {"fetch_kib": 66693.6, "write_kib": 198656.0, "traffic_bytes": 340012260,
-                    "valu_per_node": {"f32": 178.0, "f64": 6.5, "i32": 21.23, "cvt": 4.75, "i64": 1.91, "trans_f32": 13.25, "trans_f64": 0.0, "other": 38.16}},
-            "mid": {"fetch_kib": 166139.6, "write_kib": 131072.0, "traffic_bytes": 474471718,
-                    "valu_per_node": {"f32": 182.0, "f64": 16.0, "i32": 14.25, "cvt": 9.75, "i64": 2.7, "trans_f32": 13.25, "trans_f64": 0.0, "other": 27.82}},
-            "last": {"fetch_kib": 132151.2, "write_kib": 131074.2, "traffic_bytes": 404865673,
-                    "valu_per_node": {"f32": 182.0, "f64": 9.5, "i32": 13.71, "cvt": 5.25, "i64": 1.54, "trans_f32": 13.25, "trans_f64": 0.0, "other": 29.58}},
+            "pre": {"fetch_kib": 66673.6, "write_kib": 198656.0, "traffic_bytes": 339971280,
+                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 20.98, "cvt": 4.75, "i64": 1.91, "trans_f32": 13.25, "trans_f64": 0.0, "other": 40.16}},
+            "mid": {"fetch_kib": 166184.3, "write_kib": 131072.0, "traffic_bytes": 474563138,
+                    "valu_per_node": {"f32": 176.0, "f64": 16.0, "i32": 14.25, "cvt": 9.75, "i64": 2.7, "trans_f32": 13.25, "trans_f64": 0.0, "other": 29.57}},
+            "last": {"fetch_kib": 132139.4, "write_kib": 131074.2, "traffic_bytes": 404841614,
+                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 13.71, "cvt": 5.25, "i64": 1.54, "trans_f32": 13.25, "trans_f64": 0.0, "other": 31.33}},
         },
         "fp64/1024": {
-            "pre": {"fetch_kib": 4881.3, "write_kib": 25720.9, "traffic_bytes": 36335066,
-                    "valu_per_node": {"f32": 0.25, "f64": 280.0, "i32": 14.33, "cvt": 0.5, "i64": 2.48, "trans_f32": 0.25, "trans_f64": 10.75, "other": 108.94}},
-            "mid": {"fetch_kib": 17782.7, "write_kib": 10188.0, "traffic_bytes": 46851518,
-                    "valu_per_node": {"f32": 0.25, "f64": 295.5, "i32": 15.22, "cvt": 0.5, "i64": 3.67, "trans_f32": 0.25, "trans_f64": 10.81, "other": 71.4}},
-            "last": {"fetch_kib": 8863.4, "write_kib": 9866.1, "traffic_bytes": 28255028,
-                    "valu_per_node": {"f32": 0.25, "f64": 287.12, "i32": 13.96, "cvt": 0.5, "i64": 2.52, "trans_f32": 0.25, "trans_f64": 10.75, "other": 61.92}},
+            "pre": {"fetch_kib": 5726.0, "write_kib": 28800.0, "traffic_bytes": 41217962,
+                    "valu_per_node": {"f32": 0.25, "f64": 235.62, "i32": 14.33, "cvt": 0.5, "i64": 2.48, "trans_f32": 0.25, "trans_f64": 6.25, "other": 80.19}},
+            "mid": {"fetch_kib": 20018.6, "write_kib": 13824.1, "traffic_bytes": 55154057,
+                    "valu_per_node": {"f32": 0.25, "f64": 251.0, "i32": 13.78, "cvt": 0.5, "i64": 5.14, "trans_f32": 0.25, "trans_f64": 6.31, "other": 41.52}},
+            "last": {"fetch_kib": 10182.0, "write_kib": 13826.2, "traffic_bytes": 35010910,
+                    "valu_per_node": {"f32": 0.25, "f64": 242.62, "i32": 12.52, "cvt": 0.5, "i64": 3.98, "trans_f32": 0.25, "trans_f64": 6.25, "other": 32.0}},
         },
         "fp64/2048": {
-            "pre": {"fetch_kib": 17992.9, "write_kib": 102877.7, "traffic_bytes": 142196172,
-                    "valu_per_node": {"f32": 0.25, "f64": 280.0, "i32": 14.02, "cvt": 0.5, "i64": 2.18, "trans_f32": 0.25, "trans_f64": 10.75, "other": 108.51}},
-            "mid": {"fetch_kib": 68805.6, "write_kib": 40944.4, "traffic_bytes": 182840913,
-                    "valu_per_node": {"f32": 0.25, "f64": 293.62, "i32": 13.99, "cvt": 0.5, "i64": 2.38, "trans_f32": 0.25, "trans_f64": 10.75, "other": 58.97}},
-            "last": {"fetch_kib": 34431.2, "write_kib": 37658.6, "traffic_bytes": 109077438,
-                    "valu_per_node": {"f32": 0.25, "f64": 287.12, "i32": 13.55, "cvt": 0.5, "i64": 1.95, "trans_f32": 0.25, "trans_f64": 10.75, "other": 61.28}},
+            "pre": {"fetch_kib": 17264.1, "write_kib": 98816.0, "traffic_bytes": 136544521,
+                    "valu_per_node": {"f32": 0.25, "f64": 235.25, "i32": 14.02, "cvt": 0.5, "i64": 2.18, "trans_f32": 0.25, "trans_f64": 6.25, "other": 80.01}},
+            "mid": {"fetch_kib": 67598.9, "write_kib": 32768.0, "traffic_bytes": 171996904,
+                    "valu_per_node": {"f32": 0.25, "f64": 248.75, "i32": 14.24, "cvt": 0.5, "i64": 2.38, "trans_f32": 0.25, "trans_f64": 6.25, "other": 32.72}},
+            "last": {"fetch_kib": 33570.7, "write_kib": 32770.2, "traffic_bytes": 102309584,
+                    "valu_per_node": {"f32": 0.25, "f64": 242.25, "i32": 13.57, "cvt": 0.5, "i64": 1.95, "trans_f32": 0.25, "trans_f64": 6.25, "other": 34.57}},
         },
     },
 }

@@ -107,7 +107,8 @@ typedef enum {
 
 /* Options for hjw_set_option. */
 typedef enum {
-    HJW_OPT_USE_GRAPH = 0,     /* 1 (default): replay captured HIP graphs of whole RK steps;
+    HJW_OPT_USE_GRAPH = 0,     /* 1 (default): replay captured HIP graphs of whole RK steps, or
+                                  step in one launch where the grid fits on the GPU;
                                   0: launch every kernel eagerly.  Results are identical. */
     HJW_OPT_KERNEL_EVENTS = 1, /* 1: launch eagerly and bracket every kernel of a step with
                                   HIP events on the grid's stream; resets the totals that
@@ -228,7 +229,8 @@ void hjw_grid_destroy(hjw_grid *g);
  *   t_final, cfl, max_steps   as for hjw_step_to; info (host, may be NULL) as there;
  *   hip_stream                hipStream_t, borrowed (NULL: the default stream).
  * The grid's stage buffer, flux records, range slots and step records (and phi in FP32
- * storage) live in a fixed device array of the library, 32 MiB + 4 KiB, of which each
+ * storage), and the borders that tiles exchange when the grid steps in one launch, live in
+ * a fixed device array of the library, some 62 MiB, of which each
  * device the library runs on keeps one copy until the process ends.  Every call on a
  * device reuses that device's copy, so calls that overlap in time on one device race.
  * Synchronous; returns HJW_ENONFINITE if phi0 or a later value is not finite. */
