@@ -572,6 +572,24 @@ int hjw_emu_set_scheme(int scheme) {
     return 0;
 }
 
+// The march's FP64 functions of n arguments each (kind: see tests/test_fp64_math.py): out holds
+// three values per argument for kind 4, else one.
+int hjw_emu_fp64_math(int kind, int64_t n, const double* x, const double* y, const double* z,
+                      double* out) {
+    for (int64_t k = 0; k < n; ++k) {
+        switch (kind) {
+        case 0: out[k] = rcp_full(x[k]); break;
+        case 1: out[k] = quot(x[k], y[k]); break;
+        case 2: out[k] = root(x[k]); break;
+        case 3: out[k] = log_ge1(x[k]); break;
+        case 4: recip3(x[k], y[k], z[k], out[3 * k], out[3 * k + 1], out[3 * k + 2]); break;
+        case 5: out[k] = add_quot(x[k], y[k], z[k]); break;
+        default: return -1;
+        }
+    }
+    return 0;
+}
+
 // Nodes per thread in the emulated 2-D sweeps (8, or 4 with 16-row tiles), as
 // HJW_OPT_SEGMENT selects on the GPU.
 int hjw_emu_set_segment(int seg) {

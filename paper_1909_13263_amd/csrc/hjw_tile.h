@@ -187,16 +187,20 @@ __host__ __device__ inline bool finite_t(T x) {
 // they are written out from the hardware seeds instead of calling the general ones, whose
 // scaling and special cases are most of their instructions and of the FP64 kernels' code.
 // Zeros and denormals do not occur; infinities and NaNs end as NaN, which fails the step.
-// Over 2^20 arguments the seeds' relative errors stay below 5.3e-8 (2^-24).  Cell means of
+// Over 2^20 arguments the hardware seeds' relative errors stay below 5.3e-8 (2^-24); the host's
+// are cut to 24 fraction bits, so that the corrections are exercised there as well.  Cell means of
 // random pairs, wide and narrow, against extended precision: 1.2e-14 at most and 9.2e-16 rms,
 // as with the general division, sqrt and log; q + num / den: 2.2e-16 of it (2.8e-16 before).
 // They took the FP64 16-row stage kernels from 155-167 KB and 168 registers with 2-6 spilled
 // to 106-120 KB and 159-163 with none: level set 512^2 to t = 0.1 12.9 -> 8.7 ms, Burgers
 // 1024^2 16.0 -> 14.6 ms, one-sided derivatives of 1000 x 700 nodes 56 -> 41 us.
+__host__ inline double cut_seed(double x) {
+    return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) & ~0xfffffffull);
+}
 __device__ inline double rcp_seed(double x) { return __builtin_amdgcn_rcp(x); }
-__host__ inline double rcp_seed(double x) { return 1.0 / x; }
+__host__ inline double rcp_seed(double x) { return cut_seed(1.0 / x); }
 __device__ inline double rsq_seed(double x) { return __builtin_amdgcn_rsq(x); }
-__host__ inline double rsq_seed(double x) { return 1.0 / std::sqrt(x); }
+__host__ inline double rsq_seed(double x) { return cut_seed(1.0 / std::sqrt(x)); }
 
 // 1/x to about the square of the seed's error: one Newton step.
 __host__ __device__ inline double rcp_once(double x) {

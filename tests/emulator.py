@@ -38,6 +38,8 @@ def lib():
         L.hjw_emu_resident.argtypes = [ctypes.c_int, i64, i64, d, d, ctypes.c_int, ctypes.c_int,
                                        ctypes.c_int, ctypes.c_int, vp, vp, d, d, d, ctypes.c_int,
                                        ctypes.c_int, ctypes.c_int, vp]
+        L.hjw_emu_fp64_math.restype = ctypes.c_int
+        L.hjw_emu_fp64_math.argtypes = [ctypes.c_int, i64, vp, vp, vp, vp]
         _lib = L
     return _lib
 
@@ -111,3 +113,13 @@ def resident_steps(phi, h, ham, params, t, t_final, cfl, steps, tile, bc=0, prec
     rc = lib().hjw_emu_resident(dim, nx, ny, dx, dy, bx, by, prec, ham, _p(hp), _p(out), t,
                                 t_final, cfl, int(steps), tile[0], tile[1], _p(info))
     return rc, out, info
+
+
+def fp64_math(kind, x, y=None, z=None):
+    """The march's FP64 functions: 0 1/x, 1 x/y, 2 sqrt x, 3 ln x, 4 (1/x, 1/y, 1/z), 5 x + y/z."""
+    x = np.ascontiguousarray(x, dtype=np.float64)
+    y = np.ascontiguousarray(x if y is None else y, dtype=np.float64)
+    z = np.ascontiguousarray(x if z is None else z, dtype=np.float64)
+    out = np.full((x.size, 3) if kind == 4 else x.shape, np.nan)
+    assert lib().hjw_emu_fp64_math(kind, x.size, _p(x), _p(y), _p(z), _p(out)) == 0
+    return out
