@@ -214,41 +214,59 @@ __host__ __device__ inline double rcp_full(double x) {
     const double e = fma_t(-x, r, 1.0);
     return fma_t(r, fma_t(e, e, e), r);
 }
-// num/den, corrected by its own remainder.
+// num/den, corrected by its own remainder (whose own quotient needs few digits of 1/den).
 __host__ __device__ inline double quot(double num, double den) {
-    const double r = rcp_full(den);
+    const double r = rcp_once(den);
     const double q = mul_rn(num, r);
     return fma_t(fma_t(-den, q, num), r, q);
 }
-// sqrt(x), x >= 1: the coupled iteration g -> sqrt(x), h -> 1/(2 sqrt(x)) (Goldschmidt), then
-// one correction by the remainder x - g^2.
+// sqrt(x), x >= 1: one Goldschmidt step g -> sqrt(x) beside h = 1/(2 sqrt(x)), then one
+// correction by the remainder x - g^2 (below 2^-46 x, so h keeps the seed's digits).
 __host__ __device__ inline double root(double x) {
     const double y = rsq_seed(x);
-    double g = mul_rn(x, y), h = 0.5 * y;
-    const double e = fma_t(-h, g, 0.5);
-    g = fma_t(g, e, g);
-    h = fma_t(h, e, h);
+    double g = mul_rn(x, y);
+    const double h = 0.5 * y;
+    g = fma_t(g, fma_t(-h, g, 0.5), g);
     return fma_t(fma_t(-g, g, x), h, g);
 }
-// ln(y), y >= 1: y = 2^k m, m in [sqrt(1/2), sqrt(2)); ln m = 2 atanh f, f = (m-1)/(m+1), as
-// 2f + f z Q(z), z = f^2 <= 0.0295, Q the degree-6 Chebyshev fit of its series
-// 2/3 + 2z/5 + 2z^2/7 + ... on that range (relative error of ln m below 5e-18).
+// Keeps the compiler from starting what follows on x and y early.
+__device__ inline void in_order(double& x, double& y) { asm volatile("" : "+v"(x), "+v"(y)); }
+__host__ inline void in_order(double&, double&) {}
+
+// ln(y), y >= 1: y = 2^k m, m in [sqrt(1/2), sqrt(2)), d = m - 1 (exact), s = d / (2 + d); ln m =
+// 2 atanh s = d - d^2/2 + s (d^2/2 + z Q(z)), z = s^2 <= 0.0295 (since 2 s = d - s d), Q the
+// degree-6 Chebyshev fit of atanh's series 2/3 + 2z/5 + 2z^2/7 + ... on that range (relative
+// error of ln m below 5e-18).  The leading terms k ln 2, d and -d^2/2 are summed with their
+// remainders and ln 2 is a 42-bit head (its products with k are exact) and a tail, so that the
+// last sum's rounding is all but the whole error (1.03 x 2^-53 of it at most), as the library
+// logarithm's is: a mean of a narrow wide pair divides the difference of two of these by its
+// gap.  Formed as k ln 2 + (2 s + s z Q) instead, 2.8 x 2^-53, it made such means' rms error
+// 1-1.6% larger than the library functions do (second derivatives of 0.1 to 0.5); now 0.01%.
+// Against that form, FP64 runs with kinks take 3% longer (level set 512^2 7.03 -> 7.24 ms).
 __host__ __device__ inline double log_ge1(double y) {
     const uint64_t b = __builtin_bit_cast(uint64_t, y);
     const int hi = int(b >> 32);
     const int k = (hi - 0x3fe6a09e) >> 20;
     const uint64_t mb = (uint64_t(uint32_t(hi - (k << 20))) << 32) | uint32_t(b);
     const double m = __builtin_bit_cast(double, mb);
-    const double f = quot(m - 1.0, m + 1.0);
-    const double z = mul_rn(f, f);
+    double d = m - 1.0;
+    const double s = mul_rn(d, rcp_full(d + 2.0));
+    const double z = mul_rn(s, s);
     double q = fma_t(z, 0.14616585424888621989, 0.15331710618210771568);
     q = fma_t(z, q, 0.18182889455674946039);
     q = fma_t(z, q, 0.22222211130259877029);
     q = fma_t(z, q, 0.28571428626003268742);
     q = fma_t(z, q, 0.39999999999899443233);
     q = fma_t(z, q, 0.66666666666666696883);
-    const double u = fma_t(f, mul_rn(z, q), f + f);
-    return fma_t(double(k), 0.693147180559945309417, u);
+    double r = mul_rn(s, fma_t(z, q, mul_rn(0.5 * d, d)));
+    in_order(d, r);   // (else the dense kernels spill 24-35 registers, not 10-13)
+    const double half = 0.5 * d;
+    const double u = fma_t(-half, d, d);
+    r += fma_t(-half, d, d - u);
+    const double kd = double(k), head = 0x1.62e42fefa38p-1, tail = 0x1.ef35793c7673p-45;
+    const double a = fma_t(kd, head, u);
+    r = fma_t(kd, tail, r);
+    return a + ((fma_t(kd, head, -a) + u) + r);
 }
 
 // Relative half-gap below which M comes from the midpoint series, and the
@@ -285,25 +303,25 @@ __host__ __device__ inline float mean2sq_series(float sg, float dl, float q4, fl
     return mul_rn(q4 * X, X);
 }
 
-// Antiderivative of sqrt(1+s^2): (s sqrt(1+s^2) + asinh s) / 2, with
+// Twice the antiderivative of sqrt(1+s^2): s sqrt(1+s^2) + asinh s, with
 // asinh s = sign(s) ln(|s| + sqrt(1+s^2)): the logarithm's argument is >= 1 (no
 // cancellation) and the square root serves both terms.  Only pairs with a wide relative
 // gap use it, so that the difference of two values is divided by a gap of at least
 // tau sqrt(4 + sg^2): the rounding is amplified by a small factor only.
-__host__ __device__ inline double prim(double s) {
+__host__ __device__ inline double prim2(double s) {
     const double r = root(fma_t(s, s, 1.0));
-    return 0.5 * fma_t(s, r, copysign(log_ge1(fabs(s) + r), s));
+    return fma_t(s, r, copysign(log_ge1(fabs(s) + r), s));
 }
 // FP32: the same from the hardware square root and base-2 logarithm (about 1 ulp each).
-__device__ inline float prim(float s) {
+__device__ inline float prim2(float s) {
     const float r = __builtin_amdgcn_sqrtf(fmaf(s, s, 1.0f));
     const float l = __builtin_amdgcn_logf(fabsf(s) + r) * 0.693147180559945309f;
-    return 0.5f * fma_t(s, r, copysignf(l, s));
+    return fma_t(s, r, copysignf(l, s));
 }
-__host__ inline float prim(float s) {
+__host__ inline float prim2(float s) {
     const float r = std::sqrt(std::fma(s, s, 1.0f));
     const float l = std::log2(std::fabs(s) + r) * 0.693147180559945309f;
-    return 0.5f * fma_t(s, r, std::copysign(l, s));
+    return fma_t(s, r, std::copysign(l, s));
 }
 
 // Quotients: corrected by the remainder in FP64; in FP32 a product with the hardware
@@ -372,20 +390,20 @@ __host__ __device__ inline void cell_means(T c0, T b1, T c1, T f0, T& MA2, T& MB
         // only the antiderivatives of pairs that are wide on some lane (uniform tests)
         const bool wA = any_lane(xA >= tau2), wB = any_lane(xB >= tau2), wC = any_lane(xC >= tau2);
         T P0 = end.p, P1 = T(0);
-        if ((wA || wB) && !end.known) P0 = prim(c0);
+        if ((wA || wB) && !end.known) P0 = prim2(c0);
         end.known = wB || wC;
-        if (end.known) P1 = prim(c1);
+        if (end.known) P1 = prim2(c1);
         end.p = P1;
         if (wA) {
-            const T M = wdiv(T(2) * (prim(b1) - P0), dA);
+            const T M = wdiv(prim2(b1) - P0, dA);
             MA2 = xA >= tau2 ? mul_rn(M, M) : MA2;
         }
         if (wB) {
-            const T M = wdiv(T(2) * (P1 - P0), dB);
+            const T M = wdiv(P1 - P0, dB);
             MB2 = xB >= tau2 ? mul_rn(M, M) : MB2;
         }
         if (wC) {
-            const T M = wdiv(T(2) * (P1 - prim(f0)), dC);
+            const T M = wdiv(P1 - prim2(f0), dC);
             MC2 = xC >= tau2 ? mul_rn(M, M) : MC2;
         }
     } else {
