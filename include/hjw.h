@@ -156,7 +156,8 @@ hjw_status hjw_workspace_bytes(const hjw_grid *g, size_t *bytes);
 
 /* Bind device memory (>= hjw_workspace_bytes, 256-byte aligned) and a HIP stream
  * (hipStream_t; NULL lets the library create its own blocking stream).  The
- * workspace and stream are borrowed.  Rebinding is allowed; phi must be set again.
+ * workspace and stream are borrowed.  Rebinding is allowed, also to memory and a stream of
+ * another device; phi must be set again.
  * A grid small enough to be stepped in one launch (up to 1024 tiles of 64 x 16 nodes with an
  * FP32 stencil, 512 in FP64; 1-D up to 2^18 nodes) also allocates its exchange area there, at
  * most 24 MB of device memory of its own; without room for it, it steps launch by launch. */

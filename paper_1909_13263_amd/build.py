@@ -78,10 +78,24 @@ def build_c_example(out: str = C_EXAMPLE) -> str:
     return out
 
 
+HIP_STUB_SRC = os.path.join(ROOT, "tests", "host", "hip_stub.hip")
+HIP_STUB = os.path.join(ROOT, "tests", "host", "libhip_stub.so")
+
+
+def build_hip_stub(out: str = HIP_STUB) -> str:
+    """The stand-in HIP runtime of the host-code tests (test support)."""
+    tmp = out + ".tmp"
+    _run([_hipcc(), f"--offload-arch={ARCH}", "--offload-host-only", "-no-hip-rt", "-shared", *COMMON,
+          HIP_STUB_SRC, "-o", tmp])
+    os.replace(tmp, out)
+    return out
+
+
 def build_all() -> None:
     build_library()
     build_emulator()
     build_c_example()
+    build_hip_stub()
 
 
 if __name__ == "__main__":

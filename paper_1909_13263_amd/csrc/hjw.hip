@@ -60,6 +60,7 @@ struct hjw_grid {
     bool ham_set = false;
 
     // binding
+    int device = 0;      // of the stream, and so of everything the grid launches
     char* ws = nullptr;
     size_t ws_bytes = 0;
     hipStream_t stream = nullptr;
@@ -90,6 +91,7 @@ struct hjw_grid {
     bool use_resident = true;
     char* exchange = nullptr;    // its mailboxes (a bound grid's; freed with it)
     size_t exchange_bytes = 0;
+    int exchange_device = 0;
 
     // graphs
     bool use_graph = true;
@@ -197,6 +199,30 @@ hipError_t resident_bind(hjw_grid* g, char* base, size_t bytes) {
     return hipGetLastError();
 }
 
+// The device of a stream's launches (the current one's for the default stream).
+int stream_device(hipStream_t stream) {
+    int dev = 0;
+    if (stream && hipStreamGetDevice(stream, &dev) == hipSuccess) return dev;
+    (void)hipGetLastError();
+    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+    return dev;
+}
+
+// Makes a device the calling thread's current one for a scope.
+struct OnDevice {
+    int before = -1;
+    explicit OnDevice(int dev) {
+        int now = -1;
+        if (hipGetDevice(&now) == hipSuccess && now != dev && hipSetDevice(dev) == hipSuccess)
+            before = now;
+    }
+    ~OnDevice() {
+        if (before >= 0) (void)hipSetDevice(before);
+    }
+    OnDevice(const OnDevice&) = delete;
+    OnDevice& operator=(const OnDevice&) = delete;
+};
+
 // A bound grid's exchange area, of its own (it is up to 51 bytes a node on small tiles, more
 // than the caller's workspace has to spare): none where the device has no room for it, and
 // the grid then steps with the launches per stage.
@@ -209,8 +235,10 @@ hipError_t resident_alloc(hjw_grid* g) {
     ResidentArgs r{};
     int ty, seg;
     const size_t bytes = resident_area(g, &r, &ty, &seg, nullptr);
-    if (bytes != g->exchange_bytes) resident_free(g);
+    if (bytes != g->exchange_bytes || g->device != g->exchange_device) resident_free(g);
     g->exchange_bytes = bytes;
+    g->exchange_device = g->device;
+    const OnDevice on(g->device);
     if (bytes && !g->exchange &&
         hipMalloc(reinterpret_cast<void**>(&g->exchange), bytes) != hipSuccess) {
         (void)hipGetLastError();
@@ -487,9 +515,9 @@ int resident_threads(const hjw_grid* g) {
 bool resident_ready(const hjw_grid* g) {
     if (!g->resident.ctl || !g->use_resident || g->timing || g->ham == HJW_H_CURVATURE) return false;
     if (g->tile_rows != 16 || g->seg_opt || g->plan_opt) return false;
-    int dev = 0, cus = 0, per_cu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+    const OnDevice on(g->device);
+    int cus = 0, per_cu = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel(g),
                                                      resident_threads(g), 0) != hipSuccess) {
         (void)hipGetLastError();
@@ -647,6 +675,7 @@ hjw_status hjw_bind(hjw_grid* g, void* ws, size_t bytes, void* stream) {
         HIP_TRY(hipStreamCreate(&g->stream));
         g->own_stream = true;
     }
+    g->device = stream_device(g->stream);
     if (!g->pinned) HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&g->pinned), sizeof(DevState),
                                           hipHostMallocDefault));
     g->ws = static_cast<char*>(ws);
@@ -1088,6 +1117,7 @@ hjw_status hjw_solve_noalloc(int dim, const int64_t* n, const double* lo, const 
     g.nbx = nbx;
     g.nby = g.dim == 2 ? int((g.ny + g.tile_rows - 1) / g.tile_rows) : nby;
     g.stream = static_cast<hipStream_t>(stream);
+    g.device = stream_device(g.stream);
     g.use_graph = false;   // instantiating a graph allocates
     g.bound = true;
     ResidentArgs r_{};

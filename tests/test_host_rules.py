@@ -1,0 +1,48 @@
+"""Where a grid's steps go and what its launches are given, by the library's own host code on a
+stand-in HIP runtime (tests/host): no GPU, every case in a process of its own."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module", autouse=True)
+def stub():
+    from paper_1909_13263_amd import build
+    if not os.path.exists(build.HIP_STUB):
+        build.build_hip_stub()
+
+
+def _run(body):
+    code = "from rig import *\nsetup()\n" + textwrap.dedent(body)
+    r = subprocess.run([sys.executable, "-c", code], cwd=os.path.join(HERE, "host"), timeout=120,
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+def test_rebind_to_another_device_moves_the_exchange_area():
+    """After a bind to a second device every launch's mailboxes lie there, and the first
+    device's have been given back."""
+    _run("""
+        g = Grid((256, 256))
+        assert g.step(5)[0] == 0
+        assert [r[4] for r in resident(log())] == [0]
+        g.bind(1)
+        lines = log()
+        assert "free device=0" in lines and "malloc device=1" in lines, lines
+        g.set_phi()
+        assert g.step(5)[0] == 0
+        lines = log()
+        assert [r[4] for r in resident(lines)] == [1], lines
+        S.hipSetDevice(0)              # whichever device is current at the call
+        assert g.step(5)[0] == 0
+        assert [r[4] for r in resident(log())] == [1]
+        g.bind(1)                      # the same device again: the area is kept, and cleared
+        assert log() == ["clear device=1"]
+        g.close()
+        assert "free device=1" in log()
+    """)
