@@ -88,6 +88,7 @@ struct hjw_grid {
     // the launch that holds the whole grid on the chip (hjw_resident.h); null ctl: none
     ResidentArgs resident{};
     int resident_ty = 0, resident_seg = 0;
+    size_t resident_bytes = 0;   // of its exchange area, which starts at ctl
     bool use_resident = true;
     char* exchange = nullptr;    // its mailboxes (a bound grid's; freed with it)
     size_t exchange_bytes = 0;
@@ -193,6 +194,7 @@ hipError_t resident_bind(hjw_grid* g, char* base, size_t bytes) {
     if (!bytes) return hipSuccess;
     resident_area(g, &g->resident, &g->resident_ty, &g->resident_seg, base);
     g->resident.epoch = 1;
+    g->resident_bytes = bytes;
     const int64_t words = int64_t(bytes / 8);
     hipLaunchKernelGGL(k_clear_words, dim3(unsigned(std::min<int64_t>((words + 255) / 256, 1024))),
                        dim3(256), 0, g->stream, reinterpret_cast<unsigned long long*>(base), words);
@@ -789,7 +791,10 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
         if (s != HJW_OK) return s;
         if (g->last.pad[0] == 0) break;   // its workgroups did not come together: step by stages
         if (g->last.pad[0] == 2) {
+            // its tags are spent: some of its words lie in the mailboxes, others were never
+            // written, and a launch under the same tags would take them for its own
             g->failed = true;
+            HIP_TRY(resident_bind(g, reinterpret_cast<char*>(g->resident.ctl), g->resident_bytes));
             return fail(HJW_EHIP, "a workgroup stopped answering at step %lld",
                         (long long)g->last.steps);
         }

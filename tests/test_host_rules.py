@@ -46,3 +46,25 @@ def test_rebind_to_another_device_moves_the_exchange_area():
         g.close()
         assert "free device=1" in log()
     """)
+
+
+def test_a_launch_that_stopped_answering_leaves_no_tags():
+    """The words of a broken launch carry its tags: before the grid steps again in one launch,
+    the mailboxes are cleared or the tags are others."""
+    _run("""
+        g = Grid((256, 256))
+        S.stub_mode(2)
+        assert g.step(40)[0] == EHIP
+        before = log()
+        broken = resident(before)[-1]
+        S.stub_mode(0)
+        assert g.step(5)[0] != 0       # failed until phi is set again
+        g.set_phi()
+        assert g.step(5)[0] == 0
+        lines = log()
+        (after,) = resident(lines)
+        sent = next(k for k, l in enumerate(before) if "resident" in l)
+        first = next(k for k, l in enumerate(lines) if "resident" in l)
+        cleared = "clear device=0" in before[sent:] + lines[:first]
+        assert cleared or after[2] > broken[2] + broken[3], (broken, lines)
+    """)
