@@ -61,6 +61,7 @@ struct hjw_grid {
 
     // binding
     int device = 0;      // of the stream, and so of everything the grid launches
+    int units = 256;     // its compute units (a partition of a GPU has fewer)
     char* ws = nullptr;
     size_t ws_bytes = 0;
     hipStream_t stream = nullptr;
@@ -113,9 +114,6 @@ struct hjw_grid {
 
 namespace {
 
-// Compute units of the GPU that the rules below were measured on.
-constexpr int kUnits = 256;
-
 // The tile of the resident launch for this grid (hjw_resident.h): 0 where it has none.  A grid
 // takes the smallest tile that still gives at most one workgroup a compute unit, because its
 // step is then a chain of latencies (the march of a segment, the exchanges) and the shorter
@@ -128,6 +126,7 @@ constexpr int kUnits = 256;
 //                 640^2 23.8 -> 20.9   900^2 40.6 -> 35.0   1024^2 37.8 -> 29.4
 //   FP64          48^2 37.7 -> 16.3   256^2 38.0 -> 18.2 (64 x 8: 23.9)   320^2 38.4 -> 24.4
 //                 400^2 36.0 -> 32.0   512^2 27.9 -> 21.6   640^2 32.2 -> 29.2
+// Measured with 256 compute units; on a partition with fewer the same tiles a unit hold.
 int resident_tile(const hjw_grid* g, int* seg, Split* sx, Split* sy) {
     *seg = 1;
     if (g->dim == 1) {
@@ -138,10 +137,10 @@ int resident_tile(const hjw_grid* g, int* seg, Split* sx, Split* sy) {
     }
     const int64_t bx = (g->nx + kTX - 1) / kTX;
     const struct { int ty, seg; int64_t most; } option[] = {
-        {4, 0, kUnits}, {8, 2, kUnits}, {16, 4, kUnits},
-        {16, 8, g->prec == HJW_FP64 ? 2 * kUnits : 4 * kUnits}};
+        {4, 0, g->units}, {8, 2, g->units}, {16, 4, g->units},
+        {16, 8, g->prec == HJW_FP64 ? 2 * g->units : 4 * g->units}};
     for (const auto& o : option) {
-        if (bx * ((g->ny + o.ty - 1) / o.ty) > o.most) continue;
+        if (bx * ((g->ny + o.ty - 1) / o.ty) > std::min<int64_t>(o.most, kMaxResident)) continue;
         *seg = o.seg;
         *sx = split_axis(g->nx, kTX);
         *sy = split_axis(g->ny, o.ty);
@@ -208,6 +207,15 @@ int stream_device(hipStream_t stream) {
     (void)hipGetLastError();
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
     return dev;
+}
+
+int compute_units(int device) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) {
+        (void)hipGetLastError();
+        n = 0;
+    }
+    return n > 0 ? n : 256;
 }
 
 // Makes a device the calling thread's current one for a scope.
@@ -344,7 +352,7 @@ int segment(const hjw_grid* g) {
 // 4096^2 597 -> 632.
 bool dense_tiles(const hjw_grid* g) {
     const int tiles = g->nbx * g->nby;
-    return g->prec == HJW_FP64 && tiles > 3 * kUnits && tiles <= 4 * kUnits;
+    return g->prec == HJW_FP64 && tiles > 3 * g->units && tiles <= 4 * g->units;
 }
 
 template <typename T, typename P, int STAGE>
@@ -518,14 +526,13 @@ bool resident_ready(const hjw_grid* g) {
     if (!g->resident.ctl || !g->use_resident || g->timing || g->ham == HJW_H_CURVATURE) return false;
     if (g->tile_rows != 16 || g->seg_opt || g->plan_opt) return false;
     const OnDevice on(g->device);
-    int cus = 0, per_cu = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel(g),
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel(g),
                                                      resident_threads(g), 0) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    return int64_t(cus) * per_cu >= g->resident.count;
+    return int64_t(g->units) * per_cu >= g->resident.count;
 }
 
 template <typename T, typename P>
@@ -678,6 +685,7 @@ hjw_status hjw_bind(hjw_grid* g, void* ws, size_t bytes, void* stream) {
         g->own_stream = true;
     }
     g->device = stream_device(g->stream);
+    g->units = compute_units(g->device);
     if (!g->pinned) HIP_TRY(hipHostMalloc(reinterpret_cast<void**>(&g->pinned), sizeof(DevState),
                                           hipHostMallocDefault));
     g->ws = static_cast<char*>(ws);
@@ -1123,6 +1131,7 @@ hjw_status hjw_solve_noalloc(int dim, const int64_t* n, const double* lo, const 
     g.nby = g.dim == 2 ? int((g.ny + g.tile_rows - 1) / g.tile_rows) : nby;
     g.stream = static_cast<hipStream_t>(stream);
     g.device = stream_device(g.stream);
+    g.units = compute_units(g.device);
     g.use_graph = false;   // instantiating a graph allocates
     g.bound = true;
     ResidentArgs r_{};

@@ -68,3 +68,26 @@ def test_a_launch_that_stopped_answering_leaves_no_tags():
         cleared = "clear device=0" in before[sent:] + lines[:first]
         assert cleared or after[2] > broken[2] + broken[3], (broken, lines)
     """)
+
+
+def test_tiles_are_chosen_for_the_devices_own_units():
+    """On 32 compute units a grid takes the tiles that fit there (16 rows, four a unit), and FP64
+    grids of just over three tiles a unit, not of just over 768, the dense kernels."""
+    _run("""
+        setup(cus=32)
+        g = Grid((512, 256))
+        assert g.step(5)[0] == 0
+        assert [r[:2] for r in resident(log())] == [(128, 256)]
+        for shape, dense in (((1024, 1024), False), ((448, 256), True), ((512, 384), False)):
+            g = Grid(shape, FP64)
+            assert g.step(3)[0] == 0
+            lines = [l for l in log() if l.startswith("step")]
+            assert len(lines) == 3 and all(l.endswith("dense") == dense for l in lines), lines
+        setup(cus=256)
+        g = Grid((512, 256))
+        assert g.step(5)[0] == 0
+        assert [r[:2] for r in resident(log())] == [(256, 512)]   # 8 rows
+        g = Grid((1024, 1024), FP64)
+        assert g.step(3)[0] == 0
+        assert sum(l.endswith("dense") for l in log()) == 3
+    """)
