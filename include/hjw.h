@@ -125,13 +125,20 @@ typedef enum {
                                   stage, 2 in a one-wave launch of its own between the first
                                   and second stages (chosen automatically above 2048 tiles).
                                   Results are identical. */
-    HJW_OPT_DISSIPATION = 5    /* alpha of eq. (LF), alpha = max |H_1|, whose range the paper
+    HJW_OPT_DISSIPATION = 5,   /* alpha of eq. (LF), alpha = max |H_1|, whose range the paper
                                   leaves open: 0 (default) over the box of the step's
                                   derivative ranges, held for the step's three stages; 1 per
                                   node and stage over the node's own box [u-, u+] x [v-, v+]
                                   (local Lax-Friedrichs; the printed Table 2 follows it).  The
                                   time step keeps the global alpha.  Not with
                                   HJW_OPT_TILE_ROWS = 32 (EINVAL). */
+    HJW_OPT_RESIDENT = 6       /* steps of a grid that fits on the GPU: 1 (default) many in one
+                                  launch, 0 by launches per stage (a launch that fills the GPU
+                                  keeps other streams' kernels waiting until it ends).  For
+                                  tests: 2 has every such launch wait for a workgroup that is
+                                  not there, so that it gives up and the launches per stage
+                                  take over; 3 has its waits run out at once, so that
+                                  hjw_step_to fails with HJW_EHIP.  Results are identical. */
 } hjw_option;
 
 typedef struct hjw_grid hjw_grid;
@@ -191,6 +198,10 @@ hjw_status hjw_derivatives(hjw_grid *g, double *um, double *up, double *vm, doub
 
 /* Current step counters and last step's dissipation/time step. */
 hjw_status hjw_get_info(const hjw_grid *g, hjw_info *info);
+
+/* Of the steps since phi was set, those that were taken by launches of many steps
+ * (HJW_OPT_RESIDENT). */
+hjw_status hjw_resident_steps(const hjw_grid *g, int64_t *steps);
 
 hjw_status hjw_set_option(hjw_grid *g, int option, int64_t value);
 

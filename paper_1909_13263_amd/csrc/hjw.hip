@@ -90,7 +90,9 @@ struct hjw_grid {
     ResidentArgs resident{};
     int resident_ty = 0, resident_seg = 0;
     size_t resident_bytes = 0;   // of its exchange area, which starts at ctl
-    bool use_resident = true;
+    bool use_resident = true;    // off with HJW_OPT_USE_GRAPH = 0
+    int resident_opt = 1;        // HJW_OPT_RESIDENT
+    int64_t resident_steps = 0;  // steps taken by it since phi was set
     char* exchange = nullptr;    // its mailboxes (a bound grid's; freed with it)
     size_t exchange_bytes = 0;
     int exchange_device = 0;
@@ -523,7 +525,8 @@ int resident_threads(const hjw_grid* g) {
 // Whether the grid's steps can go through the resident launch: default options, a family
 // whose stencil is plus-shaped, and room on this GPU for all its workgroups at once.
 bool resident_ready(const hjw_grid* g) {
-    if (!g->resident.ctl || !g->use_resident || g->timing || g->ham == HJW_H_CURVATURE) return false;
+    if (!g->resident.ctl || !g->use_resident || !g->resident_opt) return false;
+    if (g->timing || g->ham == HJW_H_CURVATURE) return false;
     if (g->tile_rows != 16 || g->seg_opt || g->plan_opt) return false;
     const OnDevice on(g->device);
     int per_cu = 0;
@@ -548,6 +551,8 @@ hipError_t enqueue_resident(const hjw_grid* g, int64_t steps, bool set, double t
                             int64_t limit) {
     ResidentArgs r = g->resident;
     r.state = g->state;
+    r.meet = r.count + (g->resident_opt == 2 ? 1 : 0);
+    r.looks = g->resident_opt == 3 ? 0 : kMaxLooks;
     r.max_steps = int(std::min<int64_t>(steps, kResidentSteps));
     hipLaunchKernelGGL(k_resident_begin, dim3(1), dim3(64), 0, g->stream, g->state + g->par, r.ctl,
                        set ? 1 : 0, t_final, cfl, limit);
@@ -772,6 +777,7 @@ hjw_status hjw_set_phi(hjw_grid* g, const double* phi0, int on_device) {
     if (s != HJW_OK) return s;
     g->phi_set = true;
     g->failed = false;
+    g->resident_steps = 0;
     if (g->last.bad) {
         g->failed = true;
         return fail(HJW_ENONFINITE, "phi0 holds non-finite values");
@@ -809,6 +815,7 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
         const int64_t steps = g->last.steps - before;
         g->resident.epoch += unsigned(steps) + 1u;
         taken += steps;
+        g->resident_steps += steps;
         if (steps == 0 && !g->last.bad) break;
     }
     if (set) {
@@ -892,12 +899,23 @@ hjw_status hjw_get_info(const hjw_grid* g, hjw_info* info) {
     return HJW_OK;
 }
 
+hjw_status hjw_resident_steps(const hjw_grid* g, int64_t* steps) {
+    if (!g || !steps) return fail(HJW_EINVAL, "NULL argument");
+    *steps = g->resident_steps;
+    return HJW_OK;
+}
+
 hjw_status hjw_set_option(hjw_grid* g, int option, int64_t value) {
     if (!g) return fail(HJW_EINVAL, "grid is NULL");
     if (option == HJW_OPT_USE_GRAPH) {
         g->use_graph = value != 0;
         g->use_resident = value != 0;   // launch by launch, as asked
         if (!g->use_graph) drop_graph(g);
+        return HJW_OK;
+    }
+    if (option == HJW_OPT_RESIDENT) {
+        if (value < 0 || value > 3) return fail(HJW_EINVAL, "resident option must be 0 to 3");
+        g->resident_opt = int(value);
         return HJW_OK;
     }
     if (option == HJW_OPT_DISSIPATION) {

@@ -77,6 +77,8 @@ struct ResidentArgs {
     int max_steps;
     int count;                       // workgroups
     int remap;
+    int meet;                        // workgroups the rendezvous waits for
+    int looks;                       // of a wait, before it gives up
 };
 
 // One tile of the launch: its nodes and, per side, whether a neighbouring tile sends the halo
@@ -506,7 +508,7 @@ __device__ inline int resident_join(const ResidentArgs& r) {
     const unsigned int before =
         __hip_atomic_fetch_add(&r.ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned int want = 0;
-    if (before + 1 == unsigned(r.count))
+    if (before + 1 == unsigned(r.meet))
         __hip_atomic_compare_exchange_strong(&r.ctl->go, &want, 1u, __ATOMIC_RELAXED,
                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const long long t0 = wall_clock64();
@@ -532,7 +534,7 @@ __device__ inline bool wait_for(const ResidentArgs& r, Look look) {
         if ((k & 1023) == 1023 &&
             __hip_atomic_load(&r.ctl->fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u)
             return false;
-        if (k >= kMaxLooks) {
+        if (k >= r.looks) {
             __hip_atomic_store(&r.ctl->fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }

@@ -28,6 +28,7 @@ OPT_TILE_ROWS = 2
 OPT_SEGMENT = 3
 OPT_PLAN = 4
 OPT_DISSIPATION = 5
+OPT_RESIDENT = 6
 KERNEL_NAMES = ("pre", "plan", "mid", "last")
 
 PREC_NAMES = {"fp64": FP64, "fp32_mixed": FP32_MIXED, "fp32": FP32}
@@ -109,6 +110,7 @@ def lib():
             "hjw_get_phi": (ctypes.c_int, [vp, vp, ctypes.c_int]),
             "hjw_derivatives": (ctypes.c_int, [vp, vp, vp, vp, vp]),
             "hjw_get_info": (ctypes.c_int, [vp, ctypes.POINTER(_Info)]),
+            "hjw_resident_steps": (ctypes.c_int, [vp, ctypes.POINTER(i64)]),
             "hjw_set_option": (ctypes.c_int, [vp, ctypes.c_int, i64]),
             "hjw_kernel_times": (ctypes.c_int, [vp, dp, ctypes.POINTER(i64)]),
             "hjw_time_kernels": (ctypes.c_int, [vp, ctypes.c_int, dp]),
@@ -220,6 +222,12 @@ class Grid:
         ci = _Info()
         _check(lib().hjw_get_info(self._h, ctypes.byref(ci)))
         return _info(ci)
+
+    def resident_steps(self) -> int:
+        """Steps since set_phi that were taken by launches of many steps (OPT_RESIDENT)."""
+        n = ctypes.c_int64()
+        _check(lib().hjw_resident_steps(self._h, ctypes.byref(n)))
+        return int(n.value)
 
     def get_phi(self) -> np.ndarray:
         out = np.empty(self.shape, dtype=np.float64)
