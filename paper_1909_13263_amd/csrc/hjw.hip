@@ -93,6 +93,8 @@ struct hjw_grid {
     bool use_resident = true;    // off with HJW_OPT_USE_GRAPH = 0
     int resident_opt = 1;        // HJW_OPT_RESIDENT
     int64_t resident_steps = 0;  // steps taken by it since phi was set
+    int64_t pause = 0;           // steps by stages before the next try, after a meeting given up
+    int64_t next_pause = 64;
     char* exchange = nullptr;    // its mailboxes (a bound grid's; freed with it)
     size_t exchange_bytes = 0;
     int exchange_device = 0;
@@ -513,6 +515,10 @@ hjw_status enqueue_steps(hjw_grid* g, int64_t n) {
 // ------------------------------------------------------------------ the resident launch
 // Steps of one launch at most: other streams' work gets the GPU in between.
 constexpr int kResidentSteps = 256;
+// After a meeting that was given up (another process's or stream's kernels hold the GPU) the
+// grid takes so many steps by stages before it tries again, across calls, twice as many each
+// time: a caller of single steps does not pay the wait for the meeting each time.
+constexpr int64_t kFirstPause = 64, kMostPause = 4096;
 
 const void* resident_kernel(const hjw_grid* g) {
     return hjw::resident_kernel(g->prec, g->dim, g->resident_ty, g->resident_seg,
@@ -794,54 +800,60 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
     if (!std::isfinite(t_final) || !(cfl > 0.0) || !std::isfinite(cfl))
         return fail(HJW_EINVAL, "need finite t_final and cfl > 0");
     const int64_t limit = max_steps > 0 ? max_steps : std::numeric_limits<int64_t>::max();
+    const bool ready = resident_ready(g);
     int64_t taken = 0;
     bool set = true;   // the step target has still to be set
     // The host's mirror of the record is current between calls.
-    while (g->last.t < t_final && taken < limit && !g->last.bad && resident_ready(g)) {
-        HIP_TRY(enqueue_resident(g, limit - taken, set, t_final, cfl, limit));
-        set = false;
-        const int64_t before = g->last.steps;
-        s = read_state(g);
-        if (s != HJW_OK) return s;
-        if (g->last.pad[0] == 0) break;   // its workgroups did not come together: step by stages
-        if (g->last.pad[0] == 2) {
-            // its tags are spent: some of its words lie in the mailboxes, others were never
-            // written, and a launch under the same tags would take them for its own
-            g->failed = true;
-            HIP_TRY(resident_bind(g, reinterpret_cast<char*>(g->resident.ctl), g->resident_bytes));
-            return fail(HJW_EHIP, "a workgroup stopped answering at step %lld",
-                        (long long)g->last.steps);
-        }
-        const int64_t steps = g->last.steps - before;
-        g->resident.epoch += unsigned(steps) + 1u;
-        taken += steps;
-        g->resident_steps += steps;
-        if (steps == 0 && !g->last.bad) break;
-    }
-    if (set) {
-        hipLaunchKernelGGL(k_set_target, dim3(1), dim3(64), 0, g->stream, g->state + g->par,
-                           t_final, cfl, limit);
-        HIP_TRY(hipGetLastError());
-        s = read_state(g);
-        if (s != HJW_OK) return s;
-    }
     while (g->last.t < t_final && taken < limit && !g->last.bad) {
-        // Steps enqueued before the next read of the step state: one graph's worth
-        // while dt is unknown, else the estimate from the last dt plus a margin (dt
-        // shrinks as the dissipation grows).  Surplus steps find t_final reached and
-        // exit at once; a short count costs a round trip to the host.
-        int64_t n = kGraphSteps;
-        if (g->last.dt > 0.0) {
-            const double est = std::ceil((t_final - g->last.t) / g->last.dt);
-            const double want = est + std::max(2.0, std::ceil(est / 32.0));
-            n = int64_t(std::min(std::max(want, 1.0), double(kMaxBatch)));
-        }
-        n = std::min(n, limit - taken);
-        s = enqueue_steps(g, n);
-        if (s != HJW_OK) return s;
         const int64_t before = g->last.steps;
-        s = read_state(g);
-        if (s != HJW_OK) return s;
+        if (ready && g->pause == 0) {
+            HIP_TRY(enqueue_resident(g, limit - taken, set, t_final, cfl, limit));
+            set = false;
+            s = read_state(g);
+            if (s != HJW_OK) return s;
+            g->resident_steps += g->last.steps - before;
+            if (g->last.pad[0] == 1) {
+                g->resident.epoch += unsigned(g->last.steps - before) + 1u;
+                g->next_pause = kFirstPause;
+            } else if (g->last.pad[0] == 0) {   // its workgroups did not come together
+                g->pause = g->next_pause;
+                g->next_pause = std::min(2 * g->next_pause, kMostPause);
+                continue;
+            } else {
+                // its tags are spent: some of its words lie in the mailboxes, others were never
+                // written, and a launch under the same tags would take them for its own
+                g->failed = true;
+                HIP_TRY(resident_bind(g, reinterpret_cast<char*>(g->resident.ctl), g->resident_bytes));
+                return fail(HJW_EHIP, "a workgroup stopped answering at step %lld",
+                            (long long)g->last.steps);
+            }
+        } else {
+            if (set) {
+                hipLaunchKernelGGL(k_set_target, dim3(1), dim3(64), 0, g->stream, g->state + g->par,
+                                   t_final, cfl, limit);
+                HIP_TRY(hipGetLastError());
+                s = read_state(g);
+                if (s != HJW_OK) return s;
+                set = false;
+            }
+            // Steps enqueued before the next read of the step state: one graph's worth
+            // while dt is unknown, else the estimate from the last dt plus a margin (dt
+            // shrinks as the dissipation grows).  Surplus steps find t_final reached and
+            // exit at once; a short count costs a round trip to the host.
+            int64_t n = kGraphSteps;
+            if (g->last.dt > 0.0) {
+                const double est = std::ceil((t_final - g->last.t) / g->last.dt);
+                const double want = est + std::max(2.0, std::ceil(est / 32.0));
+                n = int64_t(std::min(std::max(want, 1.0), double(kMaxBatch)));
+            }
+            n = std::min(n, limit - taken);
+            if (ready) n = std::min(n, g->pause);   // then look again
+            s = enqueue_steps(g, n);
+            if (s != HJW_OK) return s;
+            s = read_state(g);
+            if (s != HJW_OK) return s;
+            g->pause = std::max<int64_t>(0, g->pause - (g->last.steps - before));
+        }
         taken += g->last.steps - before;
         if (g->last.steps == before && !g->last.bad) break;  // nothing advanced
     }

@@ -490,7 +490,7 @@ constexpr size_t mail_words(int elems) {
 
 #ifdef __HIPCC__
 // ------------------------------------------------------------------ waits (device)
-constexpr int64_t kJoinTicks = 200000;   // 2 ms of the 100 MHz wall clock
+constexpr int64_t kJoinTicks = 50000;    // 0.5 ms of the 100 MHz wall clock
 constexpr int kMaxLooks = 1 << 21;       // a second or more
 
 template <int NW>

@@ -21,7 +21,9 @@ using namespace hjw;
 namespace {
 
 int g_device = 0, g_devices = 2, g_cus = 256, g_per_cu = 4;
-int g_resident_mode = 0;       // 0 steps, 1 gives its meeting up, 2 stops answering
+// What each resident launch does: '0' steps, '1' gives its meeting up, '2' stops answering at its
+// second step; the last one for all that follow.
+std::string g_modes = "0";
 double g_dt = 1.0 / 1024;
 void (*g_hook)() = nullptr;    // called at each resident launch, before it plays
 std::string g_log;
@@ -95,13 +97,15 @@ void play(const std::string& n, const void* arg0, void** args, dim3 grid, dim3 b
         note("resident count=%d block=%u epoch=%u steps=%d mail_device=%d", r.count, block.x, r.epoch,
              r.max_steps, device_of(r.flux_mail));
         if (g_hook) g_hook();
-        if (g_resident_mode == 1) return;
+        const char mode = g_modes[0];
+        if (g_modes.size() > 1) g_modes.erase(0, 1);
+        if (mode == '1') return;
         const int par = is("Idd")   ? parity<double, double>(arg0)
                         : is("Ifd") ? parity<float, double>(arg0)
                                     : parity<float, float>(arg0);
         DevState& s = r.state[par];
         for (int k = 0; k < r.max_steps && open(s); ++k) {
-            if (g_resident_mode == 2 && k == 1) {
+            if (mode == '2' && k == 1) {
                 s.pad[0] = 2;
                 return;
             }
@@ -135,7 +139,7 @@ void stub_setup(int devices, int cus, int per_cu) {
     g_cus = cus;
     g_per_cu = per_cu;
 }
-void stub_mode(int mode) { g_resident_mode = mode; }
+void stub_modes(const char* modes) { g_modes = modes; }
 void stub_hook(void (*f)()) { g_hook = f; }
 const char* stub_log() { return g_log.c_str(); }
 void stub_clear_log() { g_log.clear(); }

@@ -53,11 +53,11 @@ def test_a_launch_that_stopped_answering_leaves_no_tags():
     the mailboxes are cleared or the tags are others."""
     _run("""
         g = Grid((256, 256))
-        S.stub_mode(2)
+        S.stub_modes(b"2")
         assert g.step(40)[0] == EHIP
         before = log()
         broken = resident(before)[-1]
-        S.stub_mode(0)
+        S.stub_modes(b"0")
         assert g.step(5)[0] != 0       # failed until phi is set again
         g.set_phi()
         assert g.step(5)[0] == 0
@@ -90,4 +90,31 @@ def test_tiles_are_chosen_for_the_devices_own_units():
         g = Grid((1024, 1024), FP64)
         assert g.step(3)[0] == 0
         assert sum(l.endswith("dense") for l in log()) == 3
+    """)
+
+
+def test_a_meeting_given_up_is_not_tried_again_at_once():
+    """After a meeting that was given up the next 64 steps go by stages, whatever the calls they
+    come in, then 128, and so on; one that is kept starts the count anew."""
+    _run("""
+        g = Grid((256, 256))
+        S.stub_modes(b"1")
+        tries, steps = [], 0
+        for k in range(500):
+            rc, info = g.step(1)
+            steps += 1
+            assert rc == 0 and info.steps == steps
+            if resident(log()):
+                tries.append(steps)
+        assert tries == [1, 65, 193, 449], tries
+        S.stub_modes(b"0")
+        assert g.step(2000)[0] == 0           # the pause runs out in it, and the meeting is kept
+        assert resident(log())
+        S.stub_modes(b"1")
+        tries, start = [], steps + 2000
+        for k in range(200):
+            rc, info = g.step(1)
+            if resident(log()):
+                tries.append(info.steps - start)
+        assert tries == [1, 65, 193], tries
     """)
