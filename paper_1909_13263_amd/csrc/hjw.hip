@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -37,6 +38,10 @@ namespace hjw {
 std::string& last_error() {
     thread_local std::string text;
     return text;
+}
+std::atomic<int>& stepping_share(int device) {
+    static std::atomic<int> share[kMaxDevices];
+    return share[device >= 0 && device < kMaxDevices ? device : 0];
 }
 }  // namespace hjw
 
@@ -202,15 +207,6 @@ hipError_t resident_bind(hjw_grid* g, char* base, size_t bytes) {
     hipLaunchKernelGGL(k_clear_words, dim3(unsigned(std::min<int64_t>((words + 255) / 256, 1024))),
                        dim3(256), 0, g->stream, reinterpret_cast<unsigned long long*>(base), words);
     return hipGetLastError();
-}
-
-// The device of a stream's launches (the current one's for the default stream).
-int stream_device(hipStream_t stream) {
-    int dev = 0;
-    if (stream && hipStreamGetDevice(stream, &dev) == hipSuccess) return dev;
-    (void)hipGetLastError();
-    if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-    return dev;
 }
 
 int compute_units(int device) {
@@ -519,6 +515,21 @@ constexpr int kResidentSteps = 256;
 // grid takes so many steps by stages before it tries again, across calls, twice as many each
 // time: a caller of single steps does not pay the wait for the meeting each time.
 constexpr int64_t kFirstPause = 64, kMostPause = 4096;
+// Steps by stages beside other calls before the grid looks whether it is alone again.
+constexpr int64_t kLookAgain = 256;
+
+// Whether the next steps go through the resident launch.  share: of the device, in thousandths,
+// 0 if they cannot; others: what this process's other stepping calls may take.
+bool resident_now(const hjw_grid* g, int share, int others) {
+    if (!share || g->pause > 0) return false;
+    // Beside other calls: only what fits on the GPU together, for launches that do not would take
+    // turns at filling it, where kernels of a stage fill each other's gaps.  us for a step of each
+    // of two grids, launches per stage | resident (FP32 stencil): 128^2 22 | 14, 800^2 44 | 68,
+    // 1024^2 52 | 71; filling it exactly, 256^2 22 | 28, 512^2 23.3 | 22.6.  FP64: 256^2 43 | 36,
+    // 512^2 45 | 41 (which fill it exactly), 640^2 55 | 74.
+    if (others && others + share > (g->prec == HJW_FP64 ? 1000 : 999)) return false;
+    return true;
+}
 
 const void* resident_kernel(const hjw_grid* g) {
     return hjw::resident_kernel(g->prec, g->dim, g->resident_ty, g->resident_seg,
@@ -528,20 +539,22 @@ int resident_threads(const hjw_grid* g) {
     return g->dim == 1 ? kResidentThreads1 : resident_threads2d(g->resident_ty, g->resident_seg);
 }
 
-// Whether the grid's steps can go through the resident launch: default options, a family
-// whose stencil is plus-shaped, and room on this GPU for all its workgroups at once.
-bool resident_ready(const hjw_grid* g) {
-    if (!g->resident.ctl || !g->use_resident || !g->resident_opt) return false;
-    if (g->timing || g->ham == HJW_H_CURVATURE) return false;
-    if (g->tile_rows != 16 || g->seg_opt || g->plan_opt) return false;
+// The part of its device that a resident launch of the grid fills, in thousandths, where the
+// steps can go through one: default options, a family whose stencil is plus-shaped, and room
+// for all its workgroups at once.  0 where they cannot.
+int resident_share(const hjw_grid* g) {
+    if (!g->resident.ctl || !g->use_resident || !g->resident_opt) return 0;
+    if (g->timing || g->ham == HJW_H_CURVATURE) return 0;
+    if (g->tile_rows != 16 || g->seg_opt || g->plan_opt) return 0;
     const OnDevice on(g->device);
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, resident_kernel(g),
                                                      resident_threads(g), 0) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return 0;
     }
-    return int64_t(g->units) * per_cu >= g->resident.count;
+    const int64_t room = int64_t(g->units) * per_cu;
+    return g->resident.count > room ? 0 : int((1000 * int64_t(g->resident.count) + room - 1) / room);
 }
 
 template <typename T, typename P>
@@ -800,13 +813,14 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
     if (!std::isfinite(t_final) || !(cfl > 0.0) || !std::isfinite(cfl))
         return fail(HJW_EINVAL, "need finite t_final and cfl > 0");
     const int64_t limit = max_steps > 0 ? max_steps : std::numeric_limits<int64_t>::max();
-    const bool ready = resident_ready(g);
+    const int share = resident_share(g);
+    const Stepping here(g->device, share ? share : 1000);
     int64_t taken = 0;
     bool set = true;   // the step target has still to be set
     // The host's mirror of the record is current between calls.
     while (g->last.t < t_final && taken < limit && !g->last.bad) {
         const int64_t before = g->last.steps;
-        if (ready && g->pause == 0) {
+        if (resident_now(g, share, here.others())) {
             HIP_TRY(enqueue_resident(g, limit - taken, set, t_final, cfl, limit));
             set = false;
             s = read_state(g);
@@ -847,7 +861,7 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
                 n = int64_t(std::min(std::max(want, 1.0), double(kMaxBatch)));
             }
             n = std::min(n, limit - taken);
-            if (ready) n = std::min(n, g->pause);   // then look again
+            if (share) n = std::min(n, g->pause > 0 ? g->pause : kLookAgain);
             s = enqueue_steps(g, n);
             if (s != HJW_OK) return s;
             s = read_state(g);
@@ -1091,7 +1105,6 @@ static_assert(align256(sizeof(RangeSlots)) + align256(2 * sizeof(DevState)) <= k
 
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
-constexpr int kMaxDevices = 64;
 std::mutex scratch_mutex;
 char* scratch_ptr[kMaxDevices] = {};
 

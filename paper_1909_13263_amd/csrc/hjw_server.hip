@@ -279,6 +279,7 @@ struct hjw_server {
     char* base = nullptr;
     size_t bytes = 0;
     hipStream_t stream = nullptr;
+    int device = 0;   // the stream's
     bool own_stream = false;
     int max_active = 0;
 
@@ -812,6 +813,7 @@ hjw_status hjw_server_create(int prec, void* pool, size_t pool_bytes, int max_ac
     for (int k = max_active - 1; k >= 0; --k) s->free_slots.push_back(k);
     hjw_status st = HJW_OK;
     s->stream = static_cast<hipStream_t>(stream);
+    s->device = stream_device(s->stream);
     if (!s->stream) {
         if (hipStreamCreate(&s->stream) != hipSuccess) st = fail(HJW_EHIP, "hipStreamCreate failed");
         s->own_stream = true;
@@ -906,6 +908,7 @@ hjw_status hjw_server_submit(hjw_server* s, const hjw_request* req, const double
 
 hjw_status hjw_server_run(hjw_server* s, int chunks, int64_t* active, int64_t* queued) {
     if (!s) return fail(HJW_EINVAL, "NULL server");
+    const Stepping here(s->device, 1000);   // grids that step meanwhile keep to launches per stage
     hjw_status st = HJW_OK;
     if (s->inflight.empty()) st = admit(s, s->up[s->step_no & 1]);
     for (int c = 0; st == HJW_OK && c < chunks && !(s->active.empty() && s->inflight.empty());

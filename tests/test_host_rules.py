@@ -93,6 +93,48 @@ def test_tiles_are_chosen_for_the_devices_own_units():
     """)
 
 
+def test_grids_that_do_not_fit_together_keep_to_launches_per_stage():
+    """A call that begins while another grid of the process is stepping on the device takes the
+    resident launch only where both fit at once."""
+    _run("""
+        for shape, fits in (((1024, 1024), False), ((128, 128), True), ((512, 512), False)):
+            a, b = Grid(shape), Grid(shape)
+            setup(per_cu=4 if shape[0] == 1024 else 2)
+            seen = []
+            @HOOK
+            def beside():
+                if not seen:
+                    seen.append(None)
+                    log()
+                    assert b.step(100)[0] == 0
+                    seen.append(log())
+            S.stub_hook(beside)
+            rc, info = a.step(100)
+            S.stub_hook(HOOK(0))
+            assert rc == 0 and info.steps == 100
+            assert bool(resident(seen[1])) == fits, (shape, seen)
+            assert staged(seen[1]) == (0 if fits else 100)
+            log()
+            assert b.step(100)[0] == 0            # alone again
+            lines = log()
+            assert staged(lines) == 0 and resident(lines)
+            other = Grid((1024, 1024), device=1)  # another device's calls are no company
+            seen.clear()
+            def elsewhere():
+                if not seen:
+                    seen.append(None)
+                    log()
+                    assert other.step(100)[0] == 0
+                    seen.append(log())
+            keep = HOOK(elsewhere)
+            S.stub_hook(keep)
+            assert a.step(100)[0] == 0
+            S.stub_hook(HOOK(0))
+            if shape[0] == 1024:
+                assert resident(seen[1])
+    """)
+
+
 def test_a_meeting_given_up_is_not_tried_again_at_once():
     """After a meeting that was given up the next 64 steps go by stages, whatever the calls they
     come in, then 128, and so on; one that is kept starts the count anew."""
