@@ -509,8 +509,14 @@ hjw_status enqueue_steps(hjw_grid* g, int64_t n) {
 }
 
 // ------------------------------------------------------------------ the resident launch
-// Steps of one launch at most: other streams' work gets the GPU in between.
-constexpr int kResidentSteps = 256;
+// Steps of one launch at most, and of one that fills more than half of the GPU: other streams'
+// kernels may get a place only in between.  64 steps of a full launch are 2.3 ms at 1024^2 (a
+// matrix product on another stream waited that long at most, 9.4 ms with 256); several such
+// launches go one behind the other before the host looks.  us a step with 64, 128, 256 steps
+// (1000 steps, FP32 stencil): 1024^2 36.9, 36.8, 36.7; 800^2 31.7, 31.4, 31.4; FP64 640^2 44.4,
+// 44.3, 44.3.
+constexpr int64_t kResidentSteps = 256, kFullSteps = 64;
+constexpr int kHalf = 500;   // thousandths
 // After a meeting that was given up (another process's or stream's kernels hold the GPU) the
 // grid takes so many steps by stages before it tries again, across calls, twice as many each
 // time: a caller of single steps does not pay the wait for the meeting each time.
@@ -565,26 +571,27 @@ hipError_t launch_resident(const hjw_grid* g, ResidentArgs r) {
                            dim3(unsigned(resident_threads(g))), args, 0, g->stream);
 }
 
-// Up to `steps` steps in one launch.  With `set`, the step target goes to the device first.
-hipError_t enqueue_resident(const hjw_grid* g, int64_t steps, bool set, double t_final, double cfl,
-                            int64_t limit) {
-    ResidentArgs r = g->resident;
+// `launches` launches of up to `steps` steps each, one behind the other.  With `set`, the step
+// target goes to the device first.
+hipError_t enqueue_resident(hjw_grid* g, int launches, int64_t steps, bool set, double t_final,
+                            double cfl, int64_t limit) {
+    ResidentArgs& r = g->resident;
     r.state = g->state;
     r.meet = r.count + (g->resident_opt == 2 ? 1 : 0);
     r.looks = g->resident_opt == 3 ? 0 : kMaxLooks;
-    r.max_steps = int(std::min<int64_t>(steps, kResidentSteps));
-    hipLaunchKernelGGL(k_resident_begin, dim3(1), dim3(64), 0, g->stream, g->state + g->par, r.ctl,
-                       set ? 1 : 0, t_final, cfl, limit);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    switch (g->prec) {
-    case HJW_FP64:
-        return launch_resident<double, double>(g, r);
-    case HJW_FP32_MIXED:
-        return launch_resident<float, double>(g, r);
-    default:
-        return launch_resident<float, float>(g, r);
+    r.max_steps = int(steps);
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < launches && e == hipSuccess; ++k) {
+        hipLaunchKernelGGL(k_resident_begin, dim3(1), dim3(64), 0, g->stream, g->state + g->par, r.ctl,
+                           set && k == 0 ? 1 : 0, t_final, cfl, limit, k > 0 ? 1 : 0);
+        e = hipGetLastError();
+        if (e != hipSuccess) break;
+        e = g->prec == HJW_FP64         ? launch_resident<double, double>(g, r)
+            : g->prec == HJW_FP32_MIXED ? launch_resident<float, double>(g, r)
+                                        : launch_resident<float, float>(g, r);
+        r.epoch += unsigned(steps) + 1u;   // one tag more than steps: of one planned and not taken
     }
+    return e;
 }
 
 hjw_status read_state(hjw_grid* g) {
@@ -820,19 +827,30 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
     // The host's mirror of the record is current between calls.
     while (g->last.t < t_final && taken < limit && !g->last.bad) {
         const int64_t before = g->last.steps;
+        // steps left, by the last dt where there is one
+        double left = double(limit - taken);
+        if (g->last.dt > 0.0)
+            left = std::min(left, std::ceil((t_final - g->last.t) / g->last.dt));
         if (resident_now(g, share, here.others())) {
-            HIP_TRY(enqueue_resident(g, limit - taken, set, t_final, cfl, limit));
+            int64_t steps = std::min(limit - taken, kResidentSteps);
+            int launches = 1;
+            if (share > kHalf && steps > kFullSteps) {
+                // (two before the first dt, which says how many it takes: one too many takes
+                // about 10 us, a look of the host 30)
+                launches = g->last.dt > 0.0 ? int(std::ceil(std::min(left, double(steps)) / kFullSteps)) : 2;
+                steps = kFullSteps;
+            }
+            HIP_TRY(enqueue_resident(g, launches, steps, set, t_final, cfl, limit));
             set = false;
             s = read_state(g);
             if (s != HJW_OK) return s;
             g->resident_steps += g->last.steps - before;
             if (g->last.pad[0] == 1) {
-                g->resident.epoch += unsigned(g->last.steps - before) + 1u;
                 g->next_pause = kFirstPause;
             } else if (g->last.pad[0] == 0) {   // its workgroups did not come together
                 g->pause = g->next_pause;
                 g->next_pause = std::min(2 * g->next_pause, kMostPause);
-                continue;
+                if (g->last.steps == before) continue;
             } else {
                 // its tags are spent: some of its words lie in the mailboxes, others were never
                 // written, and a launch under the same tags would take them for its own

@@ -688,10 +688,16 @@ __device__ inline void resident_close(const StageArgs<T, P>& a, const ResidentAr
     if (__any(bad) && threadIdx.x % 64 == 0) atomicOr(&out.bad, 1);
 }
 
-// Resets the rendezvous and the outcome; with set, also the step target.
+// Resets the rendezvous and the outcome; with set, also the step target.  With next, the launch
+// follows another whose outcome the host has not seen: unless that one ran to its end, the
+// rendezvous starts closed, and the launch leaves the outcome as it is.
 static __global__ void k_resident_begin(DevState* st, ResidentCtl* ctl, int set, double t_final,
-                                        double cfl, int64_t steps_left) {
+                                        double cfl, int64_t steps_left, int next) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
+        if (next && st->pad[0] != 1) {
+            ctl->go = 2u;
+            return;
+        }
         ctl->arrived = 0u;
         ctl->go = 0u;
         ctl->fail = 0u;

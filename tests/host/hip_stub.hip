@@ -85,6 +85,10 @@ void play(const std::string& n, const void* arg0, void** args, dim3 grid, dim3 b
     if (is("k_resident_begin")) {
         DevState* st = *static_cast<DevState**>(arg(0));
         ResidentCtl* ctl = *static_cast<ResidentCtl**>(arg(1));
+        if (*static_cast<int*>(arg(6)) && st->pad[0] != 1) {
+            ctl->go = 2;
+            return;
+        }
         *ctl = ResidentCtl{};
         st->pad[0] = 0;
         if (*static_cast<int*>(arg(2))) {
@@ -96,6 +100,7 @@ void play(const std::string& n, const void* arg0, void** args, dim3 grid, dim3 b
         const ResidentArgs& r = *static_cast<const ResidentArgs*>(arg(1));
         note("resident count=%d block=%u epoch=%u steps=%d mail_device=%d", r.count, block.x, r.epoch,
              r.max_steps, device_of(r.flux_mail));
+        if (r.ctl->go) return;
         if (g_hook) g_hook();
         const char mode = g_modes[0];
         if (g_modes.size() > 1) g_modes.erase(0, 1);

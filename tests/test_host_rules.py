@@ -160,3 +160,50 @@ def test_a_meeting_given_up_is_not_tried_again_at_once():
                 tries.append(info.steps - start)
         assert tries == [1, 65, 193], tries
     """)
+
+
+def test_a_launch_that_fills_the_gpu_is_short():
+    """Launches that fill more than half of the GPU end after 64 steps, others after 256; the tags
+    of launches that follow each other are apart."""
+    _run("""
+        for shape, prec, most in (((1024, 1024), FP32_MIXED, 64), ((256, 256), FP32_MIXED, 256),
+                                  ((640, 640), FP64, 64), ((160,), FP64, 256)):
+            setup(per_cu=2 if prec == FP64 else 4)
+            log()
+            g = Grid(shape, prec)
+            assert g.step(7)[0] == 0
+            rc, info = g.step(1000)
+            assert rc == 0 and info.steps == 1007
+            lines = log()
+            assert not staged(lines)
+            launches = resident(lines)
+            assert max(r[3] for r in launches) == most
+            for x, y in zip(launches, launches[1:]):
+                assert y[2] > x[2] + x[3]
+            rc, info = g.step(t=info.t + 99.5 * STEP)     # by time: a step to spare at most
+            assert rc == 0 and info.steps == 1107
+    """)
+
+
+def test_a_chain_of_launches_stops_at_the_first_that_does_not_meet():
+    """Launches queued behind one that gave up, or that stopped answering, do nothing."""
+    _run("""
+        g = Grid((1024, 1024))
+        assert g.step(10)[0] == 0
+        S.stub_modes(b"010")
+        rc, info = g.step(256)
+        assert rc == 0 and info.steps == 266
+        lines = log()
+        assert staged(lines) >= 64            # then by stages, and by launches again
+        taken = i64()
+        assert L.hjw_resident_steps(g.h, ctypes.byref(taken)) == 0
+        assert taken.value + staged(lines) == 266
+        S.stub_modes(b"020")
+        assert g.step(256)[0] == EHIP
+        lines = log()
+        assert lines[-1] == "clear device=0"
+        S.stub_modes(b"0")
+        g.set_phi()
+        rc, info = g.step(256)
+        assert rc == 0 and info.steps == 256
+    """)
