@@ -525,8 +525,9 @@ constexpr int64_t kFirstPause = 64, kMostPause = 4096;
 constexpr int64_t kLookAgain = 256;
 
 // Whether the next steps go through the resident launch.  share: of the device, in thousandths,
-// 0 if they cannot; others: what this process's other stepping calls may take.
-bool resident_now(const hjw_grid* g, int share, int others) {
+// 0 if they cannot; others: what this process's other stepping calls may take; left: steps to
+// go.
+bool resident_now(const hjw_grid* g, int share, int others, double left) {
     if (!share || g->pause > 0) return false;
     // Beside other calls: only what fits on the GPU together, for launches that do not would take
     // turns at filling it, where kernels of a stage fill each other's gaps.  us for a step of each
@@ -534,6 +535,10 @@ bool resident_now(const hjw_grid* g, int share, int others) {
     // 1024^2 52 | 71; filling it exactly, 256^2 22 | 28, 512^2 23.3 | 22.6.  FP64: 256^2 43 | 36,
     // 512^2 45 | 41 (which fill it exactly), 640^2 55 | 74.
     if (others && others + share > (g->prec == HJW_FP64 ? 1000 : 999)) return false;
+    // A launch that fills the GPU loads and stores all of the grid for its first step: us a call,
+    // launches per stage | resident: 1024^2 1 step 64 | 74, 2 steps 100 | 103, 3 steps 152 | 150;
+    // 900^2 68 | 76, 107 | 111, 158 | 149; 800^2 63 | 63, 101 | 93.
+    if (share > 750 && left < 3) return false;
     return true;
 }
 
@@ -831,7 +836,7 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
         double left = double(limit - taken);
         if (g->last.dt > 0.0)
             left = std::min(left, std::ceil((t_final - g->last.t) / g->last.dt));
-        if (resident_now(g, share, here.others())) {
+        if (resident_now(g, share, here.others(), left)) {
             int64_t steps = std::min(limit - taken, kResidentSteps);
             int launches = 1;
             if (share > kHalf && steps > kFullSteps) {

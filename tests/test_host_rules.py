@@ -207,3 +207,16 @@ def test_a_chain_of_launches_stops_at_the_first_that_does_not_meet():
         rc, info = g.step(256)
         assert rc == 0 and info.steps == 256
     """)
+
+
+def test_few_steps_of_a_full_grid_take_launches_per_stage():
+    _run("""
+        for shape, few in (((1024, 1024), True), ((256, 256), False)):
+            g = Grid(shape)
+            for n, by_stages in ((1, few), (2, few), (3, False)):
+                log()
+                assert g.step(n)[0] == 0
+                assert staged(log()) == (n if by_stages else 0), (shape, n)
+            rc, info = g.step(t=6 * STEP + 1.5 * STEP)      # two steps by time
+            assert rc == 0 and info.steps == 8
+    """)
