@@ -421,7 +421,7 @@ struct EmuResident {
     // Steps until t_final or `steps`; 0 done, -5 non-finite, -6 a word missing.
     int run(DevState& st, int steps) {
         for (int step = 0; step < steps && !st.bad && st.t < st.t_final; ++step) {
-            const unsigned int tag = 65530u + unsigned(step);   // crosses the 16-bit tags' end
+            const unsigned int tag = 65534u + unsigned(step);   // the third step is past 16 bits
             DevState tn = st;
             a.st = &tn;
             a.par = 0;
