@@ -157,7 +157,8 @@ typedef struct {
 hjw_status hjw_grid_create(int dim, const int64_t *n, const double *lo, const double *hi,
                            const int *bc, int prec, hjw_grid **out);
 
-/* Bytes of device workspace the grid needs (its whole HBM footprint: phi, the
+/* Bytes of device workspace the grid needs (all of its device memory but for the
+ * exchange area that hjw_bind allocates for small grids: phi, the
  * stage buffer, the three stage-1 flux arrays, block partials and the step state). */
 hjw_status hjw_workspace_bytes(const hjw_grid *g, size_t *bytes);
 
@@ -166,8 +167,9 @@ hjw_status hjw_workspace_bytes(const hjw_grid *g, size_t *bytes);
  * workspace and stream are borrowed.  Rebinding is allowed, also to memory and a stream of
  * another device; phi must be set again.
  * A grid small enough to be stepped in one launch (up to 1024 tiles of 64 x 16 nodes with an
- * FP32 stencil, 512 in FP64; 1-D up to 2^18 nodes) also allocates its exchange area there, at
- * most 24 MB of device memory of its own; without room for it, it steps launch by launch. */
+ * FP32 stencil, 512 in FP64; 1-D up to 261120 nodes; on 256 compute units) also allocates its
+ * exchange area there, at most 24 MB of device memory of its own; without room for it, it steps
+ * launch by launch. */
 hjw_status hjw_bind(hjw_grid *g, void *dev_workspace, size_t bytes, void *hip_stream);
 
 /* Choose the Hamiltonian (see hjw_ham) and its parameters (nparams <= 4). */
@@ -242,7 +244,7 @@ void hjw_grid_destroy(hjw_grid *g);
  *   hip_stream                hipStream_t, borrowed (NULL: the default stream).
  * The grid's stage buffer, flux records, range slots and step records (and phi in FP32
  * storage), and the borders that tiles exchange when the grid steps in one launch, live in
- * a fixed device array of the library, some 62 MiB, of which each
+ * a fixed device array of the library, some 55 MiB, of which each
  * device the library runs on keeps one copy until the process ends.  Every call on a
  * device reuses that device's copy, so calls that overlap in time on one device race.
  * Synchronous; returns HJW_ENONFINITE if phi0 or a later value is not finite. */

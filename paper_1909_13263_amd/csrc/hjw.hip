@@ -1117,11 +1117,15 @@ namespace {
 constexpr int64_t kNoAllocNodes = int64_t(1) << 20;   // e.g. a 1024 x 1024 grid
 constexpr size_t kNoAllocControl = 4096;               // range slots and step records
 // FP64 is the largest case: stage buffer 8 B and flux records 24 B per node.
-// The exchange area of a resident launch: mailboxes of at most 1024 tiles of 64 x 16 FP64 nodes
-// (480 elements of 8 words) and the reductions' words.
-constexpr size_t kNoAllocExchange =
-    size_t(kMaxResident) * (mail_words<double, double>(6 * (kTX + 16)) + 2 * range_words<double>()) * 8 +
-    2 * range_words<double>() * (kMaxResident / kGroup) * (kMaxResident / kGroup) * 8 + 16384;
+// The exchange area of a resident launch: the mailboxes of its 64 x 16 tiles and the reductions'
+// words, and the parts' alignment; four tiles a compute unit with an FP32 stencil, two in FP64.
+template <typename T, typename P>
+constexpr size_t exchange_bytes(size_t tiles) {
+    return tiles * (mail_words<T, P>(6 * (kTX + 16)) + 2 * range_words<T>()) * 8 +
+           2 * range_words<T>() * (kMaxResident / kGroup) * (kMaxResident / kGroup) * 8 + 16384;
+}
+constexpr size_t kNoAllocExchange = std::max(exchange_bytes<float, double>(kMaxResident),
+                                             exchange_bytes<double, double>(kMaxResident / 2));
 constexpr size_t kNoAllocBytes = size_t(kNoAllocNodes) * 32 + kNoAllocControl + kNoAllocExchange;
 static_assert(align256(sizeof(RangeSlots)) + align256(2 * sizeof(DevState)) <= kNoAllocControl,
               "control records fit");

@@ -28,6 +28,7 @@ double g_dt = 1.0 / 1024;
 void (*g_hook)() = nullptr;    // called at each resident launch, before it plays
 std::string g_log;
 std::map<const void*, std::string> g_names;
+std::map<const void*, size_t> g_vars;              // device variables' sizes
 std::map<char*, std::pair<size_t, int>> g_memory;   // base -> bytes, device
 std::map<void*, int> g_streams;
 
@@ -146,6 +147,11 @@ void stub_setup(int devices, int cus, int per_cu) {
 }
 void stub_modes(const char* modes) { g_modes = modes; }
 void stub_hook(void (*f)()) { g_hook = f; }
+size_t stub_variables() {
+    size_t sum = 0;
+    for (const auto& v : g_vars) sum += v.second;
+    return sum;
+}
 const char* stub_log() { return g_log.c_str(); }
 void stub_clear_log() { g_log.clear(); }
 void* stub_malloc(size_t bytes, int device) {
@@ -165,7 +171,9 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
                            void*, void*, void*, int*) {
     g_names[host] = name;
 }
-void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipRegisterVar(void**, void* host, char*, char*, int, size_t bytes, int, int) {
+    g_vars[host] = bytes;
+}
 
 struct Config {
     dim3 grid, block;
@@ -225,8 +233,8 @@ hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipSt
     memmove(d, s, n);
     return hipSuccess;
 }
-hipError_t hipGetSymbolAddress(void** p, const void*) {
-    *p = stub_malloc(size_t(80) << 20, g_device);
+hipError_t hipGetSymbolAddress(void** p, const void* host) {
+    *p = stub_malloc(g_vars[host], g_device);
     return hipSuccess;
 }
 hipError_t hipStreamCreate(hipStream_t* s) {

@@ -220,3 +220,25 @@ def test_few_steps_of_a_full_grid_take_launches_per_stage():
             rc, info = g.step(t=6 * STEP + 1.5 * STEP)      # two steps by time
             assert rc == 0 and info.steps == 8
     """)
+
+
+def test_the_no_allocation_solves_array_holds_every_exchange_area_and_little_more():
+    """The largest grids of each precision, tile and dimension that step in one launch do so on the
+    library's own array, which is as large as the header says."""
+    _run("""
+        S.stub_variables.restype = ctypes.c_size_t
+        assert 54 << 20 < S.stub_variables() < 56 << 20
+        for n, prec, count in (((1024, 1024), FP32_MIXED, 1024), ((1024, 1024), FP32, 1024),
+                               ((64, 16384), FP32_MIXED, 1024), ((1024, 512), FP64, 512),
+                               ((256, 256), FP64, 256), ((255 * 1024,), FP64, 1024)):
+            dim = len(n)
+            phi = S.stub_malloc(8 * n[0] * (n[1] if dim == 2 else 1), 0)
+            info = Info()
+            rc = L.hjw_solve_noalloc(
+                dim, (i64 * dim)(*n), (dbl * dim)(*[0.0] * dim), (dbl * dim)(*[1.0] * dim),
+                (ctypes.c_int * dim)(*[0] * dim), prec, 1, (dbl * 3)(1.0, 1.0, 1.0), 3, vp(phi),
+                dbl(1e9), dbl(0.5), i64(50), ctypes.byref(info), vp())
+            assert rc == 0 and info.steps == 50, L.hjw_last_error()
+            lines = log()
+            assert [r[0] for r in resident(lines)] == [count] and resident(lines)[0][4] == 0, (n, lines)
+    """)
