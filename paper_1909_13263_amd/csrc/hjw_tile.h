@@ -230,7 +230,7 @@ __host__ __device__ inline double root(double x) {
     return fma_t(fma_t(-g, g, x), h, g);
 }
 // Keeps the compiler from starting what follows on x and y early.
-__device__ inline void in_order(double& x, double& y) { asm volatile("" : "+v"(x), "+v"(y)); }
+__device__ inline void in_order(double& x, double& y) { asm("" : "+v"(x), "+v"(y)); }
 __host__ inline void in_order(double&, double&) {}
 
 // ln(y), y >= 1: y = 2^k m, m in [sqrt(1/2), sqrt(2)), d = m - 1 (exact), s = d / (2 + d); ln m =
