@@ -7,10 +7,11 @@ fused stages) runs on the GPU, from phi0 already resident in HBM.
 
 value = cells x RK stages / wall time for the FP32-stencil path (FP64 phi, FP64 time step
 and accumulation); the FP64 path is timed the same way and reported beside it.  The
-roofline object describes the dominant kernel of the launches per stage (which larger grids
-run; a 1024 x 1024 grid itself steps in one launch with its tiles in LDS), timed with HIP
-events on the library's stream right after the timed region, against the vector ALU peak
-(the bound of this path);
+roofline object describes the kernel that the timed region spends its time in, against the
+vector ALU peak (the bound of this path): where the grid steps in launches of many steps with
+its tiles in LDS (1024 x 1024 with the FP32 stencil) that launch, by the region's time a stage;
+else the dominant one of the launches per stage, timed with HIP events on the library's stream
+right after the timed region.  stage_kernel_roofline is always the latter;
 counter-derived traffic and instruction mixes ride along while the kernel sources match the
 ones they were measured on.  cpu_baseline is the
 FP64 oracle on the host cores, on a bounded sample of the same workload.
@@ -137,16 +138,17 @@ def counter_fields(rec, kernel, cells, launch_ms):
             "executed_by_class": k["valu_per_node"], "valu_busy_frac": busy}
 
 
-def alu_roofline(kernel, cells, launch_ms, prec, n):
-    """The ALU roofline object of one stage kernel: the method's 312 lane-slots per node
-    over the launch against the vector peak of its precision, with counter fields."""
+def alu_roofline(kernel, cells, launch_ms, prec, n, stage=None):
+    """The ALU roofline object of one stage kernel (or of a stage of the launch of many steps):
+    the method's 312 lane-slots per node over the launch against the vector peak of its
+    precision, with the stage kernel's counter fields."""
     fp64 = prec == "fp64"
     peak = FP64_PEAK_GOPS if fp64 else FP32_PEAK_GSLOTS
     achieved = ALGO_SLOTS_PER_CELL * cells / (launch_ms * 1e-3) / 1e9
     obj = {"bound": "alu", "kernel": kernel, "achieved": achieved, "peak": peak,
            "unit": "G FP64 lane-ops/s" if fp64 else "G lane-slots/s", "frac": achieved / peak,
            "avg_launch_ms": launch_ms, "algorithmic_slots_per_cell": ALGO_SLOTS_PER_CELL}
-    obj.update(counter_fields(measured(prec, n), kernel.split(",")[2], cells, launch_ms))
+    obj.update(counter_fields(measured(prec, n), stage, cells, launch_ms))
     return obj
 
 
@@ -155,6 +157,23 @@ def segment(n):
     grids of at most 640 tiles of 64 x 16, else 8)."""
     tiles = -(-n // 64) * -(-n // 16)
     return 4 if tiles <= 640 else 8
+
+
+def rooflines(res, prec, cells, args):
+    """(of the dominant stage kernel, of the kernel that the timed region ran)."""
+    if args.tile_rows not in (0, 16):
+        return None, None
+    types = "double,double" if prec == "fp64" else "float,double"
+    stage = max(("pre", "mid", "last"), key=lambda k: res["kernels"][k])
+    seg = 8 if prec == "fp64" else segment(args.n)
+    tiles = -(-args.n // 64) * -(-args.n // 16)
+    dense = ",dense" if prec == "fp64" and 3 * 256 < tiles <= 4 * 256 else ""
+    by_stage = alu_roofline(f"k_stage2d<{types},{stage},16,{seg}{dense}>", cells,
+                            res["kernels"][stage], prec, args.n, stage)
+    if not res["resident"]:
+        return by_stage, by_stage
+    return by_stage, alu_roofline(f"k_resident2d<{types}> (a stage of it)", cells,
+                                  res["ms_per_solve"] / res["stages"], prec, args.n)
 
 
 def kernel_source_sha():
@@ -262,13 +281,14 @@ def time_solves(hjw, pr, prec, phi_dev, steps, warmup, tile_rows=0, scheme=0):
         info = g.step_to(pr.t_final, pr.cfl)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
+    resident = 2 * g.resident_steps() > info.steps
     # kernel durations: each stage kernel launched back to back between HIP events on
     # the library's stream (queued behind a hold kernel, after two untimed launches), on
     # this grid and data, right after the timed region
     g.set_phi(phi_dev)
     times = g.time_kernels(reps=50)
     g.close()
-    return wall, info, times
+    return wall, info, times, resident
 
 
 def cpu_baseline(pr, seconds):
@@ -424,7 +444,7 @@ def beyond_mall(hjw, W, steps=3):
     step_bytes = sum(kernel_bytes_per_cell(8, 4).values()) / 3.0   # per node-stage
     dom = max(("pre", "mid", "last"), key=lambda k: times[k])
     roof = alu_roofline(f"k_stage2d<float,double,{dom},16,8>", pr.cells, times[dom],
-                        "fp32_stencil", 4096)
+                        "fp32_stencil", 4096, dom)
     rec = measured("fp32_stencil", 4096)
     hbm = None
     if rec:
@@ -564,12 +584,13 @@ def main():
     for name, prec in [("fp32", hjw.FP32_MIXED), ("fp64", hjw.FP64)]:
         if name == "fp64" and args.skip_fp64:
             continue
-        wall, info, times = time_solves(hjw, pr, prec, phi_dev, args.steps, args.warmup,
-                                        args.tile_rows)
+        wall, info, times, resident = time_solves(hjw, pr, prec, phi_dev, args.steps, args.warmup,
+                                                  args.tile_rows)
         stages = 3 * info.steps
         results[name] = {"wall": wall, "rk_steps": info.steps, "stages": stages,
                          "cell_updates_per_s": cells * stages * args.steps / wall,
-                         "ms_per_solve": 1e3 * wall / args.steps, "kernels": times}
+                         "ms_per_solve": 1e3 * wall / args.steps, "kernels": times,
+                         "resident": resident}
 
     main_res = results["fp32"]
     # dominant kernel of the FP32-stencil path
@@ -578,8 +599,7 @@ def main():
     dom_ms = ktimes[dom]
     bpc = kernel_bytes_per_cell(8, 4)[dom]
     fabric_gbs = bpc * cells / (dom_ms * 1e-3) / 1e9
-    roofline = alu_roofline(f"k_stage2d<float,double,{dom},16,{segment(args.n)}>", cells, dom_ms,
-                            "fp32_stencil", args.n) if args.tile_rows in (0, 16) else None
+    stage_roofline, roofline = rooflines(main_res, "fp32_stencil", cells, args)
     # whole-step compulsory bytes per cell-stage: (8 + 8+8 + 8+8 ... ) averaged over stages
     step_bytes = sum(kernel_bytes_per_cell(8, 4).values())
     sustained = step_bytes * cells * main_res["rk_steps"] * args.steps / main_res["wall"] / 1e9
@@ -603,6 +623,7 @@ def main():
                    "cells": cells, "rk_steps": main_res["rk_steps"],
                    "stages_per_solve": main_res["stages"]},
         "roofline": roofline,
+        "stage_kernel_roofline": stage_roofline,
         "hbm": {"kernel_GBps": fabric_gbs, "kernel_frac": fabric_gbs / HBM_PEAK_GBS,
                 "sustained_GBps": sustained, "sustained_frac": sustained / HBM_PEAK_GBS,
                 "peak_GBps": HBM_PEAK_GBS,
@@ -613,18 +634,16 @@ def main():
     }
     if "fp64" in results:
         r = results["fp64"]
-        d64 = max(("pre", "mid", "last"), key=lambda k: r["kernels"][k])
+        stage64, roofline64 = rooflines(r, "fp64", cells, args)
         line["fp64"] = {"value": r["cell_updates_per_s"], "ms_per_step": r["ms_per_solve"],
                         "rk_steps": r["rk_steps"],
                         "kernel_ms": r["kernels"],
-                        "roofline": alu_roofline(f"k_stage2d<double,double,{d64},16,8>", cells,
-                                                 r["kernels"][d64], "fp64", args.n)
-                        if args.tile_rows in (0, 16) else None}
+                        "roofline": roofline64, "stage_kernel_roofline": stage64}
         line["fp32_speedup_over_fp64"] = main_res["cell_updates_per_s"] / r["cell_updates_per_s"]
     if not args.no_jp:
         # the paper's comparison scheme on the same workload (Jiang-Peng indicators)
-        wall, info, times = time_solves(hjw, pr, hjw.FP32_MIXED, phi_dev, args.steps, args.warmup,
-                                        args.tile_rows, scheme=hjw.WENO_JP)
+        wall, info, times, _ = time_solves(hjw, pr, hjw.FP32_MIXED, phi_dev, args.steps, args.warmup,
+                                           args.tile_rows, scheme=hjw.WENO_JP)
         line["weno_jp"] = {"value": cells * 3 * info.steps * args.steps / wall,
                            "ms_per_step": 1e3 * wall / args.steps, "rk_steps": info.steps,
                            "kernel_ms": times,
