@@ -35,8 +35,9 @@ namespace hjw {
 
 // The solve that holds tile b, or -1 past the last tile.  Every lane looks at one of 64 starts,
 // so the answer is two memory round trips away (the starts are loaded beside their count) where
-// a binary search takes one per halving, all before the tile's own loads can be issued.
-// Measured (32 mixed requests served to the end, 568 steps, FP32 stencil): 27.4 -> 27.0 ms.
+// a binary search takes one per halving, all before the tile's own loads can be issued.  The
+// served time does not show it beyond its runs' spread (32 mixed requests to the end, 568 steps,
+// FP32 stencil: 27.0 to 27.5 ms with either).
 // The starts lie in whole lines of 64; what lies past the count is loaded but not looked at.
 __device__ inline int solve_of_tile(const int* tile_start, const int* ngrids, int b) {
     const int lane = int(threadIdx.x) & 63;
