@@ -627,6 +627,9 @@ def main():
         "hbm": {"kernel_GBps": fabric_gbs, "kernel_frac": fabric_gbs / HBM_PEAK_GBS,
                 "sustained_GBps": sustained, "sustained_frac": sustained / HBM_PEAK_GBS,
                 "peak_GBps": HBM_PEAK_GBS,
+                "bytes_of": "the launches per stage" + (
+                    " (the timed region's one launch keeps phi in LDS and moves borders only)"
+                    if main_res["resident"] else ""),
                 "served_from": ("Infinity Cache: the %.0f MB working set fits its 256 MB, so these "
                                 "rates are compulsory bytes over time, not HBM traffic"
                                 % (cells * 28 / 1e6)) if cells * 28 < 256e6 else "HBM"},

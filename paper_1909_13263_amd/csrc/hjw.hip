@@ -831,7 +831,8 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
     bool set = true;   // the step target has still to be set
     // The host's mirror of the record is current between calls.
     while (g->last.t < t_final && taken < limit && !g->last.bad) {
-        const int64_t before = g->last.steps;
+        const DevState last = g->last;
+        const int64_t before = last.steps;
         // steps left, by the last dt where there is one
         double left = double(limit - taken);
         if (g->last.dt > 0.0)
@@ -849,7 +850,7 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
             set = false;
             s = read_state(g);
             if (s != HJW_OK) return s;
-            g->resident_steps += g->last.steps - before;
+            if (g->last.pad[0] != 2) g->resident_steps += g->last.steps - before;
             if (g->last.pad[0] == 1) {
                 g->next_pause = kFirstPause;
             } else if (g->last.pad[0] == 0) {   // its workgroups did not come together
@@ -860,9 +861,10 @@ hjw_status hjw_step_to(hjw_grid* g, double t_final, double cfl, int64_t max_step
                 // its tags are spent: some of its words lie in the mailboxes, others were never
                 // written, and a launch under the same tags would take them for its own
                 g->failed = true;
+                g->last = last;   // (a plan made of what had come stands in the record)
                 HIP_TRY(resident_bind(g, reinterpret_cast<char*>(g->resident.ctl), g->resident_bytes));
-                return fail(HJW_EHIP, "a workgroup stopped answering at step %lld",
-                            (long long)g->last.steps);
+                return fail(HJW_EHIP, "a workgroup stopped answering after step %lld",
+                            (long long)last.steps);
             }
         } else {
             if (set) {

@@ -242,3 +242,17 @@ def test_the_no_allocation_solves_array_holds_every_exchange_area_and_little_mor
             lines = log()
             assert [r[0] for r in resident(lines)] == [count] and resident(lines)[0][4] == 0, (n, lines)
     """)
+
+
+def test_a_launch_that_stopped_answering_reports_the_record_before_it():
+    _run("""
+        g = Grid((256, 256))
+        rc, good = g.step(5)
+        assert rc == 0
+        S.stub_modes(b"2")
+        assert g.step(40)[0] == EHIP
+        info, taken = Info(), i64()
+        assert L.hjw_get_info(g.h, ctypes.byref(info)) == 0
+        assert L.hjw_resident_steps(g.h, ctypes.byref(taken)) == 0
+        assert info.steps == good.steps == taken.value == 5 and info.t == good.t
+    """)
