@@ -71,46 +71,46 @@ def kernel_bytes_per_cell(phi_b, flux_b):
 # (SQ_INSTS_VALU_* x 64 / nodes).  Valid only while the kernel sources hash to the recorded
 # SHA-256; after any change the counter-derived fields are null until re-measured.
 MEASURED = {
-    "source_sha256": "cc4418190ba68c080c2bf3bb11c4e9db6ad164036a2f77f2946d315086682c8f",
+    "source_sha256": "5aefa4f433a97dfb92789b8a3e8f01350c6be52211b969c4f7cf35a5b9a92f1b",
     "runs": {
         "fp32_stencil/1024": {
-            "pre": {"fetch_kib": 4556.3, "write_kib": 12416.0, "traffic_bytes": 22045284,
-                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 21.46, "cvt": 4.75, "i64": 2.36, "trans_f32": 13.25, "trans_f64": 0.0, "other": 40.81}},
-            "mid": {"fetch_kib": 11043.5, "write_kib": 8192.1, "traffic_bytes": 31005824,
-                    "valu_per_node": {"f32": 176.0, "f64": 17.88, "i32": 16.88, "cvt": 10.25, "i64": 3.86, "trans_f32": 13.25, "trans_f64": 0.06, "other": 35.28}},
-            "last": {"fetch_kib": 8637.0, "write_kib": 8194.2, "traffic_bytes": 26079488,
-                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 14.34, "cvt": 5.25, "i64": 2.39, "trans_f32": 13.25, "trans_f64": 0.0, "other": 32.3}},
+            "pre": {"fetch_kib": 4544.6, "write_kib": 12416.0, "traffic_bytes": 22021259,
+                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 21.46, "cvt": 4.75, "i64": 2.36, "trans_f32": 13.25, "trans_f64": 0.0, "other": 39.06}},
+            "mid": {"fetch_kib": 11017.0, "write_kib": 8192.1, "traffic_bytes": 30951552,
+                    "valu_per_node": {"f32": 176.0, "f64": 17.88, "i32": 16.88, "cvt": 10.25, "i64": 3.86, "trans_f32": 13.25, "trans_f64": 0.06, "other": 33.53}},
+            "last": {"fetch_kib": 8648.5, "write_kib": 8194.2, "traffic_bytes": 26103040,
+                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 14.34, "cvt": 5.25, "i64": 2.39, "trans_f32": 13.25, "trans_f64": 0.0, "other": 30.55}},
         },
         "fp32_stencil/2048": {
-            "pre": {"fetch_kib": 17060.3, "write_kib": 49664.0, "traffic_bytes": 85795403,
-                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 21.14, "cvt": 4.75, "i64": 2.06, "trans_f32": 13.25, "trans_f64": 0.0, "other": 40.38}},
-            "mid": {"fetch_kib": 42238.0, "write_kib": 32768.0, "traffic_bytes": 120057832,
-                    "valu_per_node": {"f32": 176.0, "f64": 16.0, "i32": 14.25, "cvt": 9.75, "i64": 2.91, "trans_f32": 13.25, "trans_f64": 0.0, "other": 29.77}},
-            "last": {"fetch_kib": 33423.5, "write_kib": 32770.2, "traffic_bytes": 102008101,
-                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 13.92, "cvt": 5.25, "i64": 1.83, "trans_f32": 13.25, "trans_f64": 0.0, "other": 31.66}},
+            "pre": {"fetch_kib": 17046.2, "write_kib": 49664.0, "traffic_bytes": 85766532,
+                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 21.14, "cvt": 4.75, "i64": 2.06, "trans_f32": 13.25, "trans_f64": 0.0, "other": 38.63}},
+            "mid": {"fetch_kib": 42212.8, "write_kib": 32768.0, "traffic_bytes": 120006229,
+                    "valu_per_node": {"f32": 176.0, "f64": 16.0, "i32": 14.25, "cvt": 9.75, "i64": 2.91, "trans_f32": 13.25, "trans_f64": 0.0, "other": 28.02}},
+            "last": {"fetch_kib": 33439.4, "write_kib": 32770.2, "traffic_bytes": 102040599,
+                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 13.92, "cvt": 5.25, "i64": 1.83, "trans_f32": 13.25, "trans_f64": 0.0, "other": 29.91}},
         },
         "fp32_stencil/4096": {
-            "pre": {"fetch_kib": 66673.6, "write_kib": 198656.0, "traffic_bytes": 339971280,
-                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 20.98, "cvt": 4.75, "i64": 1.91, "trans_f32": 13.25, "trans_f64": 0.0, "other": 40.16}},
-            "mid": {"fetch_kib": 166184.3, "write_kib": 131072.0, "traffic_bytes": 474563138,
-                    "valu_per_node": {"f32": 176.0, "f64": 16.0, "i32": 14.25, "cvt": 9.75, "i64": 2.7, "trans_f32": 13.25, "trans_f64": 0.0, "other": 29.57}},
-            "last": {"fetch_kib": 132139.4, "write_kib": 131074.2, "traffic_bytes": 404841614,
-                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 13.71, "cvt": 5.25, "i64": 1.54, "trans_f32": 13.25, "trans_f64": 0.0, "other": 31.33}},
+            "pre": {"fetch_kib": 66650.5, "write_kib": 198656.0, "traffic_bytes": 339924062,
+                    "valu_per_node": {"f32": 172.0, "f64": 6.5, "i32": 20.98, "cvt": 4.75, "i64": 1.91, "trans_f32": 13.25, "trans_f64": 0.0, "other": 38.41}},
+            "mid": {"fetch_kib": 166112.2, "write_kib": 131072.0, "traffic_bytes": 474415540,
+                    "valu_per_node": {"f32": 176.0, "f64": 16.0, "i32": 14.25, "cvt": 9.75, "i64": 2.7, "trans_f32": 13.25, "trans_f64": 0.0, "other": 27.82}},
+            "last": {"fetch_kib": 132162.6, "write_kib": 131074.2, "traffic_bytes": 404888974,
+                    "valu_per_node": {"f32": 176.0, "f64": 9.5, "i32": 13.71, "cvt": 5.25, "i64": 1.54, "trans_f32": 13.25, "trans_f64": 0.0, "other": 29.58}},
         },
         "fp64/1024": {
-            "pre": {"fetch_kib": 5726.0, "write_kib": 28800.0, "traffic_bytes": 41217962,
+            "pre": {"fetch_kib": 5995.5, "write_kib": 29824.0, "traffic_bytes": 42818522,
                     "valu_per_node": {"f32": 0.25, "f64": 235.62, "i32": 14.33, "cvt": 0.5, "i64": 2.48, "trans_f32": 0.25, "trans_f64": 6.25, "other": 80.19}},
-            "mid": {"fetch_kib": 20018.6, "write_kib": 13824.1, "traffic_bytes": 55154057,
-                    "valu_per_node": {"f32": 0.25, "f64": 251.0, "i32": 13.78, "cvt": 0.5, "i64": 5.14, "trans_f32": 0.25, "trans_f64": 6.31, "other": 41.52}},
-            "last": {"fetch_kib": 10182.0, "write_kib": 13826.2, "traffic_bytes": 35010910,
-                    "valu_per_node": {"f32": 0.25, "f64": 242.62, "i32": 12.52, "cvt": 0.5, "i64": 3.98, "trans_f32": 0.25, "trans_f64": 6.25, "other": 32.0}},
+            "mid": {"fetch_kib": 20204.3, "write_kib": 14848.1, "traffic_bytes": 56582949,
+                    "valu_per_node": {"f32": 0.25, "f64": 251.0, "i32": 13.78, "cvt": 0.5, "i64": 5.14, "trans_f32": 0.25, "trans_f64": 6.31, "other": 41.77}},
+            "last": {"fetch_kib": 10230.1, "write_kib": 14850.2, "traffic_bytes": 36157852,
+                    "valu_per_node": {"f32": 0.25, "f64": 242.62, "i32": 12.52, "cvt": 0.5, "i64": 3.98, "trans_f32": 0.25, "trans_f64": 6.25, "other": 32.5}},
         },
         "fp64/2048": {
-            "pre": {"fetch_kib": 17264.1, "write_kib": 98816.0, "traffic_bytes": 136544521,
+            "pre": {"fetch_kib": 17237.7, "write_kib": 98816.0, "traffic_bytes": 136490448,
                     "valu_per_node": {"f32": 0.25, "f64": 235.25, "i32": 14.02, "cvt": 0.5, "i64": 2.18, "trans_f32": 0.25, "trans_f64": 6.25, "other": 80.01}},
-            "mid": {"fetch_kib": 67598.9, "write_kib": 32768.0, "traffic_bytes": 171996904,
+            "mid": {"fetch_kib": 67636.8, "write_kib": 32768.0, "traffic_bytes": 172074628,
                     "valu_per_node": {"f32": 0.25, "f64": 248.75, "i32": 14.24, "cvt": 0.5, "i64": 2.38, "trans_f32": 0.25, "trans_f64": 6.25, "other": 32.72}},
-            "last": {"fetch_kib": 33570.7, "write_kib": 32770.2, "traffic_bytes": 102309584,
+            "last": {"fetch_kib": 33592.0, "write_kib": 32770.2, "traffic_bytes": 102353175,
                     "valu_per_node": {"f32": 0.25, "f64": 242.25, "i32": 13.57, "cvt": 0.5, "i64": 1.95, "trans_f32": 0.25, "trans_f64": 6.25, "other": 34.57}},
         },
     },

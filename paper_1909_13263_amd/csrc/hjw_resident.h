@@ -21,15 +21,14 @@
 // than kJoinTicks closes it, whereupon every workgroup (also one that starts later) leaves
 // without having changed anything and the host steps with the launches per stage.  Once all
 // have arrived every later wait ends; the waits are bounded all the same.
-// What bounds it.  On small grids a step is a chain of latencies: with a march of two nodes a
-// thread, 256^2 (256 tiles of 64 x 4, FP32 stencil) took 14.2 us a step = sweeps 2.9, finishes
-// and phi_1 3.0, the box's two hops and the plan 4.3, two border exchanges 3.0 and barriers; a
-// hop between two workgroups, store to load, takes about 1.5 us, the plan's FP64 chain 0.7.  At 1024^2 (four 64 x 16 tiles a compute unit) it is the issue of
-// vector instructions: a wave instruction takes 4 cycles of its SIMD here (the counters give
-// 1.04 quad-cycles each), so the 1200 instructions of a wave and stage make 24 of the 30 us a
-// step; the launches per stage take 38.  Whole solves, launches per stage -> this launch:
-// Burgers 1024^2 8.1 -> 6.5 ms (FP32 stencil), 1-D N = 160 0.92 -> 0.26 ms, Dirichlet 80^2 FP64
-// 7.9 -> 2.9 ms, level set 512^2 FP64 8.7 -> 7.0 ms.
+// What bounds it.  On small grids a step is a chain of latencies: 256^2 (256 tiles of 64 x 4, FP32
+// stencil) takes 14.3 us a step = sweeps 1.9, finishes and phi_1 2.8, the box reduced over all tiles
+// and the plan 5.1, two border exchanges 3.0, barriers and the rest 1.5.  At 1024^2 (four 64 x 16
+// tiles a compute unit) it is the issue of vector instructions: a wave instruction takes 4 cycles
+// of its SIMD here (the counters give 1.04 quad-cycles each), and they keep the vector units busy
+// for 0.88 of the launch; the launches per stage take 38 us a step, this one 30.  Whole solves,
+// launches per stage -> this launch: Burgers 1024^2 8.1 -> 6.6 ms (FP32 stencil), 1-D N = 160
+// 0.92 -> 0.26 ms, Dirichlet 80^2 FP64 7.9 -> 3.0 ms, level set 512^2 FP64 8.7 -> 7.2 ms.
 // Nodes' results and phi^n stay in LDS, not in registers, from sweep to finish: with them in
 // registers the unrolled finishes of three stages and all families were 118 KB of code with
 // scratch traffic, and a 1024^2 step took 50 us.  Borders are sent from LDS in the mailboxes'

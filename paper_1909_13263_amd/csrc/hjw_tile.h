@@ -91,7 +91,7 @@ constexpr int kTX1 = 1024, kS1 = 4;
 // Threads of a 2-D workgroup: as many row threads as column threads.
 constexpr int threads2d(int ty, int seg) { return 2 * (kTX / seg) * ty; }
 // Waves per SIMD asked of the FP64 16-row stage kernels, which is also the tiles a CU holds:
-// three (VGPRs <= 168, none spilled), or four of the dense kernels (<= 128, 8-11 spilled, and
+// three (VGPRs <= 168, none spilled), or four of the dense kernels (<= 128, 10-13 spilled, and
 // no copy of phi^n in LDS).
 constexpr int fp64_waves(int elem, int ty, bool dense) {
     return elem == 8 && ty == 16 ? (dense ? 4 : 3) : 1;
@@ -188,12 +188,13 @@ __host__ __device__ inline bool finite_t(T x) {
 // scaling and special cases are most of their instructions and of the FP64 kernels' code.
 // Zeros and denormals do not occur; infinities and NaNs end as NaN, which fails the step.
 // Over 2^20 arguments the hardware seeds' relative errors stay below 5.3e-8 (2^-24); the host's
-// are cut to 24 fraction bits, so that the corrections are exercised there as well.  Cell means of
-// random pairs, wide and narrow, against extended precision: 1.2e-14 at most and 9.2e-16 rms,
-// as with the general division, sqrt and log; q + num / den: 2.2e-16 of it (2.8e-16 before).
+// are cut to 24 fraction bits, so that the corrections are exercised there as well.  One-sided
+// derivatives of rough data (h = 1/64, second derivatives of 0.003 to 1000) against extended
+// precision: 0.998 to 1.0004 of the rms error that the general division, sqrt and log leave.
 // They took the FP64 16-row stage kernels from 155-167 KB and 168 registers with 2-6 spilled
-// to 106-120 KB and 159-163 with none: level set 512^2 to t = 0.1 12.9 -> 8.7 ms, Burgers
-// 1024^2 16.0 -> 14.6 ms, one-sided derivatives of 1000 x 700 nodes 56 -> 41 us.
+// to 118-132 KB and 143-147 with none: level set 512^2 to t = 0.1 12.9 -> 8.7 ms, Burgers
+// 1024^2 16.0 -> 14.6 ms, one-sided derivatives of 1000 x 700 nodes 56 -> 41 us (by launches per
+// stage).
 __host__ inline double cut_seed(double x) {
     return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, x) & ~0xfffffffull);
 }
