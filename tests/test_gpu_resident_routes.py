@@ -121,3 +121,45 @@ def test_graph_replays_at_both_parities_are_the_eager_launches(prec):
         assert np.array_equal(grids[0].get_phi(), grids[1].get_phi())
         _ = grids[0].derivatives()
     assert grids[0].resident_steps() == grids[1].resident_steps() == 0
+
+
+def test_a_server_and_a_grid_step_at_the_same_time():
+    """A server drains a batch in one thread while a grid that fills the GPU steps in another:
+    both give the bits that they give alone, whichever routes the grid takes."""
+    import threading
+
+    import torch
+    problems = [W.burgers2d(200 + 40 * k, 0.02) for k in range(6)]
+    pr = W.burgers2d(1024)
+
+    def serve(out):
+        st = torch.cuda.Stream()
+        srv = hjw.Server(MIXED, pool_bytes=256 << 20, max_active=16, stream=st.cuda_stream)
+        for _ in range(3):
+            ids = [srv.submit(p) for p in problems]
+            done = {r.rid: r.phi for r in srv.drain()}
+            out.append([done[i] for i in ids])
+        srv.close()
+
+    def step(out):
+        st = torch.cuda.Stream()
+        g = hjw.grid_for(pr, MIXED, stream=st.cuda_stream)
+        g.set_phi(pr.phi0())
+        for n in (1, 70, 200, 2, 5):
+            out.append((g.step_to(1.0, 0.5, max_steps=n), g.get_phi()))
+        g.close()
+
+    alone, together = ([], []), ([], [])
+    serve(alone[0])
+    step(alone[1])
+    threads = [threading.Thread(target=serve, args=(together[0],)),
+               threading.Thread(target=step, args=(together[1],))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(together[0]) == len(alone[0]) and len(together[1]) == len(alone[1])
+    for a, b in zip(alone[0], together[0]):
+        assert all(np.array_equal(x, y) for x, y in zip(a, b))
+    for (ia, pa), (ib, pb) in zip(alone[1], together[1]):
+        assert ia == ib and np.array_equal(pa, pb)
